@@ -26,93 +26,16 @@
 //     indices; the per-token loop broadcasts them with v_readlane, so the ids live in SGPRs.
 //   * Per token-layer and lane: k conflict-free LDS reads (64 consecutive dwords per wave), OR of the
 //     masks, then (rarely) the replicated slots, then two popcounts into per-lane accumulators.
-#include "tacg_internal.h"
+#include "eval_internal.h"
 
 namespace tacg {
 namespace {
 
 constexpr int kMainThreads = 1024;
-constexpr int kMaxPieces = 160;
-constexpr uint32_t kXcds = 8;  // XCDs of an MI355X; workgroups are dealt to them round-robin
 // About 32 workgroups of ev_main per CU: short enough that the last round leaves little idle time
 // when the families' ragged last pieces make the workgroups uneven (measured 2 % faster than 4096
 // on a Dirichlet family mix), long enough to amortise the table set-up and the flushes.
 constexpr int64_t kTargetWorkgroups = 8192;
-constexpr uint8_t kNone = 0xFF;
-
-struct EvWs {
-  uint32_t* cnt;        // [L][E] dispatches per expert
-  uint32_t* flagbits;   // [L][8] experts with a secondary in some placement
-  uint8_t* rep_of;      // [L][E] compact replicated index or 0xFF
-  int32_t* rep_list;    // [L][TACG_MAX_REPLICATED]
-  int32_t* n_rep;       // [L]
-  uint2* rep_info;      // [L][TACG_MAX_REPLICATED][P]  (FC mask, fallback GPU)
-  // accumulators are laid out with the placement fastest, so that a workgroup's adds for its run of
-  // placements are contiguous (coalesced atomics)
-  unsigned long long* acc_home;  // [P]
-  unsigned long long* acc_span;  // [P]
-  unsigned long long* acc_fam;   // [F][P]
-  uint32_t* rep_load;   // [L][G][P2], P2 = P rounded up to even: placement pairs share a 64-bit add
-  // App. C statistics (used only by tacg_eval_trace_stats)
-  uint32_t* cnt_fam;                  // [F][L][E] dispatches per expert and family
-  unsigned long long* acc_span_fam;   // [F][P] sum of |cards| over the family's token-layers
-  unsigned long long* acc_cross_fam;  // [F][P] token-layers whose cards span several bands
-  unsigned long long* acc_hmass_fam;  // [F][P] replicated-slot dispatches served in the family's band
-  unsigned long long* n_bad;          // [1] token-layers not scored: an id out of range or repeated
-  uint32_t* bad_tiles;                // [ceil(N L / 64 / 32)] bit g: token-layers 64 g .. 64 g + 63 of
-                                      // the flattened trace (x = l N + t) hold an invalid one
-};
-
-__host__ __device__ inline int32_t even_up(int32_t P) { return P + (P & 1); }
-
-__host__ __device__ inline int64_t bad_tile_words(int64_t N, int32_t L) { return (N * L + 2047) / 2048; }
-
-EvWs carve_ev(void* ws, int64_t N, int32_t L, int32_t E, int32_t G, int32_t P, int32_t F, size_t* used = nullptr) {
-  Carver c{static_cast<char*>(ws), 0};
-  EvWs r;
-  r.cnt = c.take<uint32_t>(static_cast<size_t>(L) * E);
-  r.flagbits = c.take<uint32_t>(static_cast<size_t>(L) * 8);
-  r.acc_home = c.take<unsigned long long>(static_cast<size_t>(P));
-  r.acc_span = c.take<unsigned long long>(static_cast<size_t>(P));
-  r.acc_fam = c.take<unsigned long long>(static_cast<size_t>(P) * F);
-  r.rep_load = c.take<uint32_t>(static_cast<size_t>(even_up(P)) * L * G);
-  r.rep_of = c.take<uint8_t>(static_cast<size_t>(L) * E);
-  r.rep_list = c.take<int32_t>(static_cast<size_t>(L) * TACG_MAX_REPLICATED);
-  r.n_rep = c.take<int32_t>(static_cast<size_t>(L));
-  r.rep_info = c.take<uint2>(static_cast<size_t>(L) * TACG_MAX_REPLICATED * P);
-  r.cnt_fam = c.take<uint32_t>(static_cast<size_t>(F) * L * E);
-  r.acc_span_fam = c.take<unsigned long long>(static_cast<size_t>(P) * F);
-  r.acc_cross_fam = c.take<unsigned long long>(static_cast<size_t>(P) * F);
-  r.acc_hmass_fam = c.take<unsigned long long>(static_cast<size_t>(P) * F);
-  r.n_bad = c.take<unsigned long long>(1);
-  r.bad_tiles = c.take<uint32_t>(static_cast<size_t>(bad_tile_words(N, L)));
-  if (used) *used = c.used;
-  return r;
-}
-
-struct EvArgs {
-  const int16_t* trace;
-  const uint8_t* primary;
-  const uint8_t* secondary;
-  const int64_t* load_ref;
-  uint32_t* d_err;
-  EvWs ws;
-  int64_t N;
-  int32_t L, K, E, F, G, P, R;
-  int32_t theta_num, theta_den;
-  int32_t n_pieces;
-  int32_t n_pblocks;  // placement blocks of 64 * PPL placements
-  int32_t stats;      // App. C statistics requested
-  uint32_t band_starts;  // bit b: a family band starts at GPU b (the bands tile 0..G-1)
-  // home band of family f: component f % 4 of band4[f / 4] = home_start | home_size << 8
-  uint4 band4[TACG_MAX_FAMILIES / 4];
-  // One record per piece of one family's tokens: (first token, end token, family offset,
-  // home_start | home_size << 8 | family << 16).  Kept as 16-byte records: indexing kernel-argument
-  // arrays of different element sizes with one runtime index lets the compiler fold the byte and
-  // dword offsets into an unaligned scalar-load base, which the scalar unit does not honour.
-  uint4 piece[kMaxPieces];
-};
-static_assert(sizeof(EvArgs) <= 4096, "kernel arguments must stay within 4 KB");
 
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void ev_zero(EvArgs a) {
@@ -843,12 +766,14 @@ int launch_main(const EvArgs& a, int n_pblocks, hipStream_t stream) {
 }
 
 template <int K>
+void launch_valid(const EvArgs& a, hipStream_t stream) {
+  const int64_t groups = (a.N * a.L + 63) / 64;  // one wave per 64 token-layers, four waves per block
+  const int blocks = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(8192, (groups + 3) / 4)));
+  hipLaunchKernelGGL(ev_valid<K>, dim3(blocks), dim3(256), 0, stream, a);
+}
+
+template <int K>
 int launch_main_k(const EvArgs& a, hipStream_t stream) {
-  {
-    const int64_t groups = (a.N * a.L + 63) / 64;  // one wave per 64 token-layers, four waves per block
-    const int blocks = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(8192, (groups + 3) / 4)));
-    hipLaunchKernelGGL(ev_valid<K>, dim3(blocks), dim3(256), 0, stream, a);
-  }
   // the statistics variant exists for two placements per lane only (it is not on the timed path)
   if (a.stats) return launch_main<K, 2, true>(a, (a.P + 127) / 128, stream);
   if (a.E > 64) return launch_main<K, 2, false>(a, (a.P + 127) / 128, stream);
@@ -994,11 +919,14 @@ int launch_eval(const int16_t* trace, int64_t N, int32_t L, int32_t K, int32_t E
   if (R > 0) hipLaunchKernelGGL(ev_repinfo, dim3((P + 255) / 256, L), dim3(256), 0, stream, a);
   if (hipGetLastError() != hipSuccess) return TACG_E_DEVICE;
   if (np > 0) {
+    const bool planes = stats == nullptr && eval_uses_planes(K, E, G);
     int rc;
     switch (K) {
 #define TACG_K(k) \
   case k:         \
-    rc = launch_main_k<k>(a, stream); \
+    launch_valid<k>(a, stream);  \
+    rc = planes ? launch_eval_planes(a, fam_off_host, home_start_host, home_size_host, stream) \
+                : launch_main_k<k>(a, stream); \
     break;
       TACG_K(1) TACG_K(2) TACG_K(3) TACG_K(4) TACG_K(5) TACG_K(6) TACG_K(7) TACG_K(8)
       TACG_K(9) TACG_K(10) TACG_K(11) TACG_K(12) TACG_K(13) TACG_K(14) TACG_K(15) TACG_K(16)

@@ -1,0 +1,91 @@
+// Declarations shared by the placement-scoring kernels (eval.hip, eval_planes.hip): the workspace layout and
+// the arguments of the passes around the trace pass.
+#pragma once
+
+#include "tacg_internal.h"
+
+namespace tacg {
+
+constexpr uint8_t kNone = 0xFF;
+constexpr int kMaxPieces = 160;
+constexpr uint32_t kXcds = 8;  // XCDs of an MI355X; workgroups are dealt to them round-robin
+struct EvWs {
+  uint32_t* cnt;        // [L][E] dispatches per expert
+  uint32_t* flagbits;   // [L][8] experts with a secondary in some placement
+  uint8_t* rep_of;      // [L][E] compact replicated index or 0xFF
+  int32_t* rep_list;    // [L][TACG_MAX_REPLICATED]
+  int32_t* n_rep;       // [L]
+  uint2* rep_info;      // [L][TACG_MAX_REPLICATED][P]  (FC mask, fallback GPU)
+  // accumulators are laid out with the placement fastest, so that a workgroup's adds for its run of
+  // placements are contiguous (coalesced atomics)
+  unsigned long long* acc_home;  // [P]
+  unsigned long long* acc_span;  // [P]
+  unsigned long long* acc_fam;   // [F][P]
+  uint32_t* rep_load;   // [L][G][P2], P2 = P rounded up to even: placement pairs share a 64-bit add
+  // App. C statistics (used only by tacg_eval_trace_stats)
+  uint32_t* cnt_fam;                  // [F][L][E] dispatches per expert and family
+  unsigned long long* acc_span_fam;   // [F][P] sum of |cards| over the family's token-layers
+  unsigned long long* acc_cross_fam;  // [F][P] token-layers whose cards span several bands
+  unsigned long long* acc_hmass_fam;  // [F][P] replicated-slot dispatches served in the family's band
+  unsigned long long* n_bad;          // [1] token-layers not scored: an id out of range or repeated
+  uint32_t* bad_tiles;                // [ceil(N L / 64 / 32)] bit g: token-layers 64 g .. 64 g + 63 of
+                                      // the flattened trace (x = l N + t) hold an invalid one
+};
+
+__host__ __device__ inline int32_t even_up(int32_t P) { return P + (P & 1); }
+
+__host__ __device__ inline int64_t bad_tile_words(int64_t N, int32_t L) { return (N * L + 2047) / 2048; }
+
+inline EvWs carve_ev(void* ws, int64_t N, int32_t L, int32_t E, int32_t G, int32_t P, int32_t F, size_t* used = nullptr) {
+  Carver c{static_cast<char*>(ws), 0};
+  EvWs r;
+  r.cnt = c.take<uint32_t>(static_cast<size_t>(L) * E);
+  r.flagbits = c.take<uint32_t>(static_cast<size_t>(L) * 8);
+  r.acc_home = c.take<unsigned long long>(static_cast<size_t>(P));
+  r.acc_span = c.take<unsigned long long>(static_cast<size_t>(P));
+  r.acc_fam = c.take<unsigned long long>(static_cast<size_t>(P) * F);
+  r.rep_load = c.take<uint32_t>(static_cast<size_t>(even_up(P)) * L * G);
+  r.rep_of = c.take<uint8_t>(static_cast<size_t>(L) * E);
+  r.rep_list = c.take<int32_t>(static_cast<size_t>(L) * TACG_MAX_REPLICATED);
+  r.n_rep = c.take<int32_t>(static_cast<size_t>(L));
+  r.rep_info = c.take<uint2>(static_cast<size_t>(L) * TACG_MAX_REPLICATED * P);
+  r.cnt_fam = c.take<uint32_t>(static_cast<size_t>(F) * L * E);
+  r.acc_span_fam = c.take<unsigned long long>(static_cast<size_t>(P) * F);
+  r.acc_cross_fam = c.take<unsigned long long>(static_cast<size_t>(P) * F);
+  r.acc_hmass_fam = c.take<unsigned long long>(static_cast<size_t>(P) * F);
+  r.n_bad = c.take<unsigned long long>(1);
+  r.bad_tiles = c.take<uint32_t>(static_cast<size_t>(bad_tile_words(N, L)));
+  if (used) *used = c.used;
+  return r;
+}
+
+struct EvArgs {
+  const int16_t* trace;
+  const uint8_t* primary;
+  const uint8_t* secondary;
+  const int64_t* load_ref;
+  uint32_t* d_err;
+  EvWs ws;
+  int64_t N;
+  int32_t L, K, E, F, G, P, R;
+  int32_t theta_num, theta_den;
+  int32_t n_pieces;
+  int32_t n_pblocks;  // placement blocks of 64 * PPL placements
+  int32_t stats;      // App. C statistics requested
+  uint32_t band_starts;  // bit b: a family band starts at GPU b (the bands tile 0..G-1)
+  // home band of family f: component f % 4 of band4[f / 4] = home_start | home_size << 8
+  uint4 band4[TACG_MAX_FAMILIES / 4];
+  // One record per piece of one family's tokens: (first token, end token, family offset,
+  // home_start | home_size << 8 | family << 16).  Kept as 16-byte records: indexing kernel-argument
+  // arrays of different element sizes with one runtime index lets the compiler fold the byte and
+  // dword offsets into an unaligned scalar-load base, which the scalar unit does not honour.
+  uint4 piece[kMaxPieces];
+};
+static_assert(sizeof(EvArgs) <= 4096, "kernel arguments must stay within 4 KB");
+
+// The bit-plane trace pass (eval_planes.hip): whether it takes these sizes, and its launch.
+bool eval_uses_planes(int32_t top_k, int32_t n_experts, int32_t n_gpus);
+int launch_eval_planes(const EvArgs& e, const int64_t* fam_off_host, const int32_t* home_start_host,
+                       const int32_t* home_size_host, hipStream_t stream);
+
+}  // namespace tacg
