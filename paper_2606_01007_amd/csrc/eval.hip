@@ -780,27 +780,61 @@ int launch_main_k(const EvArgs& a, hipStream_t stream) {
   return launch_main<K, 4, false>(a, (a.P + 255) / 256, stream);
 }
 
-// per-(placement, layer) primary-only loads from D.  grid (P, L), 256 threads.
-__global__ __launch_bounds__(256) void placement_load_kernel(const uint32_t* __restrict__ D, int F, int L, int E,
-                                                             const uint8_t* __restrict__ primary, int G,
-                                                             int64_t* __restrict__ load_ref, uint32_t* d_err) {
-  __shared__ unsigned long long acc[TACG_MAX_GPUS];
-  const int p = blockIdx.x, l = blockIdx.y;
-  if (threadIdx.x < G) acc[threadIdx.x] = 0;
-  __syncthreads();
-  uint32_t err = 0;
+// Per-(placement, layer) primary-only loads from D.  A workgroup takes one layer and a run of placements: it sums
+// the families' dispatches of every expert once, then each wave scores placements of its own, lanes over experts,
+// into its own counters (64-bit LDS adds).  Bound by the latency of the table rows (four byte loads per
+// placement, the next placement's in flight) and by LDS adds on few addresses.  Measured on MI355X at E = 256, 32
+// GPUs, 16 families, 1024 placements x 58 layers: 140 -> 19 us (one workgroup per (placement, layer)
+// summed the families again each time).
+constexpr int kLoadWaves = 8;
+constexpr int kLoadRun = 64;  // placements per workgroup
+
+__global__ __launch_bounds__(64 * kLoadWaves) void placement_load_kernel(const uint32_t* __restrict__ D, int F, int L,
+                                                                         int E, const uint8_t* __restrict__ primary,
+                                                                         int P, int G, int64_t* __restrict__ load_ref,
+                                                                         uint32_t* d_err) {
+  __shared__ unsigned long long acc[kLoadWaves][TACG_MAX_GPUS];
+  __shared__ unsigned long long sum[TACG_MAX_EXPERTS];
+  const int l = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int e = threadIdx.x; e < E; e += blockDim.x) {
-    const uint8_t g = primary[(static_cast<int64_t>(p) * L + l) * E + e];
-    if (g >= G) {
-      err |= TACG_ERR_TABLE;
-      continue;
-    }
     unsigned long long s = 0;
+#pragma unroll 8
     for (int f = 0; f < F; ++f) s += D[(static_cast<int64_t>(f) * L + l) * E + e];
-    if (s) atomicAdd(&acc[g], s);
+    sum[e] = s;
   }
-  barrier_after_lds_atomics();
-  if (threadIdx.x < G) load_ref[(static_cast<int64_t>(p) * L + l) * G + threadIdx.x] = static_cast<int64_t>(acc[threadIdx.x]);
+  __syncthreads();
+  unsigned long long d[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) d[q] = lane + 64 * q < E ? sum[lane + 64 * q] : 0ull;
+  const int p1 = min(P, static_cast<int>(blockIdx.x + 1) * kLoadRun);
+  uint32_t err = 0;
+  uint8_t next[4];
+  auto fetch = [&](int p) {
+    const uint8_t* src = primary + (static_cast<int64_t>(min(p, P - 1)) * L + l) * E;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) next[q] = src[min(lane + 64 * q, E - 1)];
+  };
+  int p = blockIdx.x * kLoadRun + wave;
+  fetch(p);
+  for (; p < p1; p += kLoadWaves) {
+    uint32_t g[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) g[q] = next[q];
+    fetch(p + kLoadWaves);
+    if (lane < G) acc[wave][lane] = 0;
+    __asm__ __volatile__("" ::: "memory");  // the LDS keeps a wave's operations in order
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (lane + 64 * q >= E) continue;
+      if (g[q] >= static_cast<uint32_t>(G)) {
+        err |= TACG_ERR_TABLE;
+      } else if (d[q]) {
+        __hip_atomic_fetch_add(&acc[wave][g[q]], d[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+    __asm__ __volatile__("" ::: "memory");
+    if (lane < G) load_ref[(static_cast<int64_t>(p) * L + l) * G + lane] = static_cast<int64_t>(acc[wave][lane]);
+  }
   if (err) atomicOr(d_err, err);
 }
 
@@ -946,7 +980,8 @@ int launch_eval(const int16_t* trace, int64_t N, int32_t L, int32_t K, int32_t E
 
 int launch_placement_load(const uint32_t* D, int32_t F, int32_t L, int32_t E, const uint8_t* primary, int32_t P,
                           int32_t G, int64_t* load_ref, uint32_t* d_err, hipStream_t stream) {
-  hipLaunchKernelGGL(placement_load_kernel, dim3(P, L), dim3(256), 0, stream, D, F, L, E, primary, G, load_ref, d_err);
+  hipLaunchKernelGGL(placement_load_kernel, dim3((P + kLoadRun - 1) / kLoadRun, L), dim3(64 * kLoadWaves), 0, stream, D, F, L,
+                     E, primary, P, G, load_ref, d_err);
   return hipGetLastError() == hipSuccess ? TACG_OK : TACG_E_DEVICE;
 }
 
