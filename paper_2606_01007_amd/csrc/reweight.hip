@@ -2,29 +2,31 @@
 // usage-coact-advantage, coact-advantage, zscore, soft-score, family-pref, same-family-kernel,
 // task-modulated-graph).  Internal arithmetic is float64; outputs are float32.
 //
-// Four passes per call (all small next to the trace passes; C is read once):
-//   rw_nf     grid (L, F), one wave each: N_f = sum_i D_f[i] / k of every (layer, family).
+// Three passes per call (all small next to the trace passes; C is read once):
 //   rw_rows   grid (L, row blocks): per row i and family f the co-activation strength
 //             c_f(i) = sum_{j != i} C_f[i][j] / N_f, the pooled A-bar[i][j] = mean_f C_f[i][j] / N_f
-//             (zero diagonal) and the layer maximum of A-bar (atomic max on the float64 bit pattern,
-//             valid because every value is >= 0).  A wave reads the row of eight families at once.
-//   rw_z      grid (L, F), one thread per expert: usage u_f = D_f / (N_f k), advantages against the
-//             mean of the other families, z-scores over experts (population std), s = z(du) + z(dc).
-//   rw_graph  grid (L, row blocks): the softmax over f of the layer's scores into LDS (the first row
-//             block also writes the preferences), then A-hat = A-bar / max, A_task = P P^T, A-tilde.
+//             (zero diagonal) and the row block's maximum of A-bar.  A wave per eight families, summed by halving
+//             exchanges; the next row's loads are in flight.
+//   rw_pref   grid (L): usage u_f = D_f / (N_f k), advantages against the mean of the other families, z-scores over
+//             experts (population std; a wave per family), s = z(du) + z(dc), the softmax over f of the
+//             layer's scores and the layer maximum of A-bar.
+//   rw_graph  grid (L, row blocks): A-hat = A-bar / max, A_task = P P^T, A-tilde; a wave holds four rows x four
+//             columns per lane, so each preference read from LDS serves four products.
+// Bound by the read of C (rw_rows: 243 MB at E = 256, 16 families, 58 layers).  Measured on MI355X at that size, whole
+// call: 119 -> 102 us (a pass of its own for N_f, the softmax repeated in every row block of the graph
+// pass, a preference read per product).
 #include "tacg_internal.h"
 
 namespace tacg {
 namespace {
 
-constexpr int kRows = 16;  // rows of a layer per workgroup in rw_rows / rw_graph
+constexpr int kRows = 16;  // most rows of a layer per workgroup (rw_graph: always)
 
 struct RwWs {
   double* c;          // [L][F][E]
   double* abar;       // [L][E][E]
-  uint64_t* maxbits;  // [L]
-  double* s;          // [L][F][E]  soft scores divided by tau
-  double* nf;         // [L][F]     tokens per family
+  double* max;        // [L]        maximum of A-bar
+  double* s;          // [L][F][E]  maxima of the row blocks (from the layer's first entry on), then preferences
 };
 
 RwWs carve_rw(void* ws, int32_t F, int32_t L, int32_t E, size_t* used = nullptr) {
@@ -32,9 +34,8 @@ RwWs carve_rw(void* ws, int32_t F, int32_t L, int32_t E, size_t* used = nullptr)
   RwWs r;
   r.c = c.take<double>(static_cast<size_t>(L) * F * E);
   r.abar = c.take<double>(static_cast<size_t>(L) * E * E);
-  r.maxbits = c.take<uint64_t>(static_cast<size_t>(L));
+  r.max = c.take<double>(static_cast<size_t>(L));
   r.s = c.take<double>(static_cast<size_t>(L) * F * E);
-  r.nf = c.take<double>(static_cast<size_t>(L) * F);
   if (used) *used = c.used;
   return r;
 }
@@ -51,188 +52,37 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
-// Sum over the workgroup (blockDim.x a multiple of 64, <= 1024); every thread gets the result.
-__device__ double block_sum(double v, double* red) {
-  v = wave_sum(v);
+constexpr int kSums = 8;  // values summed over the wave together, and family rows of C held by a wave
+
+// One halving exchange between lanes 8 M apart: the lower lane keeps values 0 .. M - 1 of both, the upper one M .. 2 M - 1.
+template <int M>
+__device__ __forceinline__ void halve(double* x) {
+  const bool up = (threadIdx.x & (8 * M)) != 0;
+#pragma unroll
+  for (int i = 0; i < M; ++i) {
+    const double keep = up ? x[i + M] : x[i], send = up ? x[i] : x[i + M];
+    x[i] = keep + __shfl_xor(send, 8 * M, 64);
+  }
+}
+
+// Sums x[0..7] over the wave: every lane gets the sum of value (lane >> 3) & 7.  Ten exchanges against 48 for
+// eight separate sums.
+__device__ __forceinline__ double wave_sum8(double (&x)[kSums]) {
+  halve<4>(x);
+  halve<2>(x);
+  halve<1>(x);
+  double s = x[0];
+  s += __shfl_xor(s, 4, 64);
+  s += __shfl_xor(s, 2, 64);
+  s += __shfl_xor(s, 1, 64);
+  return s;
+}
+
+// 1 / N_f of the layer's families (0 for an empty one) into inv_n, N_f into nf if wanted: one wave per family, an
+// exact integer sum over the experts.  The caller synchronises.
+__device__ __forceinline__ void family_tokens(const uint32_t* __restrict__ D, int F, int L, int E, int k, int l,
+                                              double* inv_n, double* nf) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  __syncthreads();
-  if (lane == 0) red[wave] = v;
-  __syncthreads();
-  double t = 0.0;
-  for (int i = 0; i < nw; ++i) t += red[i];
-  return t;
-}
-
-// N_f of every (layer, family): one wave per pair, lanes over experts (an exact integer sum); the
-// (l, 0) wave also clears the layer's maximum.
-__global__ __launch_bounds__(64) void rw_nf(const uint32_t* __restrict__ D, int F, int L, int E, int k, RwWs ws) {
-  const int l = blockIdx.x, f = blockIdx.y, lane = threadIdx.x;
-  const uint32_t* d = D + (static_cast<int64_t>(f) * L + l) * E;
-  unsigned long long s = 0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int e = lane + 64 * q;
-    if (e < E) s += d[e];
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
-  if (lane == 0) {
-    ws.nf[static_cast<int64_t>(l) * F + f] = static_cast<double>(s) / k;
-    if (f == 0) ws.maxbits[l] = 0;
-  }
-}
-
-constexpr int kFamChunk = 8;  // family rows of C read together in rw_rows
-
-__global__ __launch_bounds__(256) void rw_rows(const uint32_t* __restrict__ C, int F, int L, int E, RwWs ws) {
-  __shared__ double inv_n[TACG_MAX_FAMILIES];
-  const int l = blockIdx.x;
-  for (int f = threadIdx.x; f < F; f += blockDim.x) {
-    const double n = ws.nf[static_cast<int64_t>(l) * F + f];
-    inv_n[f] = n > 0 ? 1.0 / n : 0.0;
-  }
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  const int r0 = blockIdx.y * kRows, r1 = min(E, r0 + kRows);
-  double mx = 0.0;
-  for (int i = r0 + wave; i < r1; i += nw) {
-    double ab[4] = {0, 0, 0, 0};
-    for (int f0 = 0; f0 < F; f0 += kFamChunk) {
-      // the row of up to eight families in flight (family index clamped into range)
-      uint32_t v[kFamChunk][4];
-#pragma unroll
-      for (int u = 0; u < kFamChunk; ++u) {
-        const int f = min(f0 + u, F - 1);
-        const uint32_t* row = C + ((static_cast<int64_t>(f) * L + l) * E + i) * E;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[u][q] = row[min(lane + 64 * q, E - 1)];
-      }
-#pragma unroll
-      for (int u = 0; u < kFamChunk; ++u) {
-        const int f = f0 + u;
-        if (f >= F) break;
-        double rs = 0.0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int j = lane + 64 * q;
-          if (j < E && j != i) {
-            const double a = v[u][q] * inv_n[f];
-            rs += a;
-            ab[q] += a;
-          }
-        }
-        rs = wave_sum(rs);
-        if (lane == 0) ws.c[(static_cast<int64_t>(l) * F + f) * E + i] = rs;
-      }
-    }
-    double* arow = ws.abar + (static_cast<int64_t>(l) * E + i) * E;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int j = lane + 64 * q;
-      if (j < E) {
-        const double v = ab[q] / F;
-        arow[j] = v;
-        mx = fmax(mx, v);
-      }
-    }
-  }
-  mx = wave_max(mx);
-  if (lane == 0 && mx > 0.0) atomicMax(reinterpret_cast<unsigned long long*>(ws.maxbits + l),
-                                       static_cast<unsigned long long>(__double_as_longlong(mx)));
-}
-
-// One workgroup per (layer, family), one thread per expert (E <= 256 = blockDim): the family's
-// soft score s / tau of every expert.
-__global__ __launch_bounds__(256) void rw_z(const uint32_t* __restrict__ D, int F, int L, int E, int k,
-                                            double tau, double eps, RwWs ws) {
-  __shared__ double red[16];
-  const int l = blockIdx.x, f = blockIdx.y;
-  const int e = threadIdx.x;
-  const bool on = e < E;
-  const double* nf = ws.nf + static_cast<int64_t>(l) * F;
-  double du = 0.0, dc = 0.0;
-  if (on) {
-    // sums over families of u and c for this expert, in family order
-    double su = 0.0, sc = 0.0, uf = 0.0, cf = 0.0;
-    for (int g = 0; g < F; ++g) {
-      const double n = nf[g];
-      const double u = n > 0 ? D[(static_cast<int64_t>(g) * L + l) * E + e] / (n * k) : 0.0;
-      const double c = ws.c[(static_cast<int64_t>(l) * F + g) * E + e];
-      su += u;
-      sc += c;
-      if (g == f) {
-        uf = u;
-        cf = c;
-      }
-    }
-    du = uf - (su - uf) / (F - 1);
-    dc = cf - (sc - cf) / (F - 1);
-  }
-  const double mu_u = block_sum(on ? du : 0.0, red) / E;
-  const double mu_c = block_sum(on ? dc : 0.0, red) / E;
-  const double vu = block_sum(on ? (du - mu_u) * (du - mu_u) : 0.0, red) / E;
-  const double vc = block_sum(on ? (dc - mu_c) * (dc - mu_c) : 0.0, red) / E;
-  if (on) {
-    const double z = (du - mu_u) / (sqrt(vu) + eps) + (dc - mu_c) / (sqrt(vc) + eps);
-    ws.s[(static_cast<int64_t>(l) * F + f) * E + e] = z / tau;
-  }
-}
-
-__global__ __launch_bounds__(256) void rw_graph(int F, int L, int E, double alpha, float* __restrict__ pref,
-                                                float* __restrict__ a_tilde, float* __restrict__ a_hat, RwWs ws) {
-  extern __shared__ double P[];  // [F][E] preferences of the layer
-  const int l = blockIdx.x;
-  // softmax over families of the scores, one thread per expert
-  {
-    const int e = threadIdx.x;
-    if (e < E) {
-      const double* sl = ws.s + static_cast<int64_t>(l) * F * E;
-      double zmax = -INFINITY;
-      for (int f = 0; f < F; ++f) zmax = fmax(zmax, sl[f * E + e]);
-      double den = 0.0;
-      for (int f = 0; f < F; ++f) den += exp(sl[f * E + e] - zmax);
-      for (int f = 0; f < F; ++f) {
-        const double p = exp(sl[f * E + e] - zmax) / den;
-        P[f * E + e] = p;
-        if (blockIdx.y == 0) pref[(static_cast<int64_t>(l) * E + e) * F + f] = static_cast<float>(p);
-      }
-    }
-  }
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  const double mx = __longlong_as_double(static_cast<long long>(ws.maxbits[l]));
-  const double inv = mx > 0.0 ? 1.0 / mx : 0.0;
-  const int r0 = blockIdx.y * kRows, r1 = min(E, r0 + kRows);
-  for (int i = r0 + wave; i < r1; i += nw) {
-    const double* arow = ws.abar + (static_cast<int64_t>(l) * E + i) * E;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int j = lane + 64 * q;
-      if (j >= E) continue;
-      const double ah = mx > 0.0 ? arow[j] * inv : 0.0;
-      double task = 0.0;
-      for (int f = 0; f < F; ++f) task += P[f * E + i] * P[f * E + j];
-      const double at = (1.0 - alpha) * ah + alpha * (task * ah);
-      const int64_t o = (static_cast<int64_t>(l) * E + i) * E + j;
-      a_tilde[o] = static_cast<float>(at);
-      if (a_hat) a_hat[o] = static_cast<float>(ah);
-    }
-  }
-}
-
-// GESR identification scores (Sec. 3.4, eq. generic-score) per row i of layer l, float64:
-// Cent = sum_j A-bar(i, j); Cons = mean_f cos(A_f(i, :), A-bar(i, :)) (0 for a zero row);
-// Spec = max_f ||A_f(i, :) - A-bar(i, :)||_2.  One wave per row, lanes over columns; the family rows
-// are read twice (once for A-bar, once for the per-family terms), eight families' rows in flight at a
-// time.  grid (L, row blocks), 256 threads.
-__global__ __launch_bounds__(256) void gesr_scores_kernel(const uint32_t* __restrict__ D,
-                                                          const uint32_t* __restrict__ C, int F, int L, int E, int k,
-                                                          double* __restrict__ cent, double* __restrict__ cons,
-                                                          double* __restrict__ spec) {
-  __shared__ double inv_n[TACG_MAX_FAMILIES];
-  const int l = blockIdx.x;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  // N_f of the layer: one wave per family, an exact integer sum over the experts
   for (int f = wave; f < F; f += nw) {
     const uint32_t* d = D + (static_cast<int64_t>(f) * L + l) * E;
     unsigned long long t = 0;
@@ -244,79 +94,345 @@ __global__ __launch_bounds__(256) void gesr_scores_kernel(const uint32_t* __rest
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) t += __shfl_xor(t, o, 64);
     const double n = static_cast<double>(t) / k;
-    if (lane == 0) inv_n[f] = n > 0 ? 1.0 / n : 0.0;
-  }
-  __syncthreads();
-  const int r0 = blockIdx.y * kRows, r1 = min(E, r0 + kRows);
-  // the rows of families f0 .. f0 + 7 of row i (family index clamped into range)
-  auto load_rows = [&](int i, int f0, uint32_t (&v)[kFamChunk][4]) {
-#pragma unroll
-    for (int u = 0; u < kFamChunk; ++u) {
-      const int f = min(f0 + u, F - 1);
-      const uint32_t* row = C + ((static_cast<int64_t>(f) * L + l) * E + i) * E;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) v[u][q] = row[min(lane + 64 * q, E - 1)];
+    if (lane == 0) {
+      inv_n[f] = n > 0 ? 1.0 / n : 0.0;
+      if (nf) nf[f] = n;
     }
-  };
-  for (int i = r0 + wave; i < r1; i += nw) {
-    double ab[4] = {0, 0, 0, 0};
-    for (int f0 = 0; f0 < F; f0 += kFamChunk) {
-      uint32_t v[kFamChunk][4];
-      load_rows(i, f0, v);
+  }
+}
+
+// One wave's share of the family rows of C: families f0 .. f0 + 7 (f0 = 8 wave) of a row, four columns per lane.
+struct FamRows {
+  double inv[kSums];       // 1 / N_f (0 for an empty family or past F)
+  const uint32_t* base;    // row 0 of family f0
+  int64_t stride;          // between families
+  int E, n;                // n: families of this wave
+  uint32_t next[kSums][4];
+
+  __device__ __forceinline__ void init(const uint32_t* D, const uint32_t* C, int F, int L, int E_, int k, int l, int f0) {
+    const int lane = threadIdx.x & 63;
+    E = E_;
+    n = min(kSums, F - f0);
+    stride = static_cast<int64_t>(L) * E * E;
+    base = C + (static_cast<int64_t>(f0) * L + l) * E * E;
 #pragma unroll
-      for (int u = 0; u < kFamChunk; ++u) {
-        const int f = f0 + u;
-        if (f >= F) break;
+    for (int u = 0; u < kSums; ++u) {
+      const uint32_t* d = D + (static_cast<int64_t>(f0 + min(u, n - 1)) * L + l) * E;
+      unsigned long long t = 0;  // an exact integer sum over the experts
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int j = lane + 64 * q;
-          if (j < E && j != i) ab[q] += v[u][q] * inv_n[f];
-        }
+      for (int q = 0; q < 4; ++q) t += lane + 64 * q < E ? d[min(lane + 64 * q, E - 1)] : 0u;
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) t += __shfl_xor(t, o, 64);
+      const double nf = static_cast<double>(t) / k;
+      inv[u] = u < n && nf > 0 ? 1.0 / nf : 0.0;
+    }
+  }
+  __device__ __forceinline__ void fetch(int i) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int u = 0; u < kSums; ++u) {
+      const uint32_t* row = base + min(u, n - 1) * stride + static_cast<int64_t>(i) * E;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) next[u][q] = row[min(lane + 64 * q, E - 1)];
+    }
+  }
+  // the fetched rows, the diagonal and columns past E as zero
+  __device__ __forceinline__ void take(int i, uint32_t (&v)[kSums][4]) const {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const bool on = lane + 64 * q < E && lane + 64 * q != i;
+#pragma unroll
+      for (int u = 0; u < kSums; ++u) v[u][q] = on ? next[u][q] : 0u;
+    }
+  }
+};
+
+// Workgroups of ceil(F / 8) waves, one row of A-bar at a time: every wave scales its families' rows, the waves' parts of
+// the row meet in LDS (two buffers in turn, one barrier a row), and the next row's loads are in flight meanwhile.
+// grid (L, row blocks); dynamic LDS: 2 x waves x E doubles.
+__global__ __launch_bounds__(512) void rw_rows(const uint32_t* __restrict__ D, const uint32_t* __restrict__ C, int F,
+                                               int L, int E, int k, int rows, RwWs ws) {
+  extern __shared__ double part[];  // [2][nw][E]
+  __shared__ double wmax[TACG_MAX_FAMILIES / kSums];
+  const int l = blockIdx.x, nw = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r0 = blockIdx.y * rows, r1 = min(E, r0 + rows);
+  FamRows fr;
+  fr.init(D, C, F, L, E, k, l, kSums * wave);
+  fr.fetch(r0);
+  double mx = 0.0;
+  for (int i = r0; i < r1; ++i) {
+    uint32_t v[kSums][4];
+    fr.take(i, v);
+    fr.fetch(min(i + 1, E - 1));
+    double* const mine = part + static_cast<size_t>(((i & 1) * nw + wave)) * E;
+    double x[kSums], ab[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int u = 0; u < kSums; ++u) {
+      x[u] = 0.0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const double a = v[u][q] * fr.inv[u];
+        x[u] += a;
+        ab[q] += a;
       }
     }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (lane + 64 * q < E) mine[lane + 64 * q] = ab[q];
+    const double c = wave_sum8(x);
+    if ((lane & 7) == 0 && (lane >> 3) < fr.n)
+      ws.c[(static_cast<int64_t>(l) * F + kSums * wave + (lane >> 3)) * E + i] = c;
+    __syncthreads();
+    const double* const all = part + static_cast<size_t>((i & 1) * nw) * E;
+    for (int j = threadIdx.x; j < E; j += blockDim.x) {
+      double t = 0.0;
+      for (int w = 0; w < nw; ++w) t += all[w * E + j];
+      t /= F;
+      ws.abar[(static_cast<int64_t>(l) * E + i) * E + j] = t;
+      mx = fmax(mx, t);
+    }
+  }
+  mx = wave_max(mx);
+  if (lane == 0) wmax[wave] = mx;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < nw; ++w) mx = fmax(mx, wmax[w]);
+    // a layer of s has F E >= 2 E entries, more than its row blocks
+    ws.s[static_cast<int64_t>(l) * F * E + blockIdx.y] = mx;
+  }
+}
+
+constexpr int kPrefThreads = 1024;
+
+// One workgroup per layer.  LDS: scores [F][E], then per expert the sums over families [4][E] of u and of c.
+__global__ __launch_bounds__(kPrefThreads) void rw_pref(const uint32_t* __restrict__ D, int F, int L, int E, int k,
+                                                        double tau, double eps, int row_blocks, float* __restrict__ pref,
+                                                        RwWs ws) {
+  extern __shared__ double sc[];
+  __shared__ double inv_n[TACG_MAX_FAMILIES], nf[TACG_MAX_FAMILIES];
+  double* const sum_u = sc + static_cast<size_t>(F) * E;  // [4][E], then in [0][E] the maximum over f
+  double* const sum_c = sum_u + 4 * static_cast<size_t>(E);  // [4][E], then in [0][E] the softmax denominator
+  const int l = blockIdx.x, tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  constexpr int kWaves = kPrefThreads / 64;
+  double* const sl = ws.s + static_cast<int64_t>(l) * F * E;
+  const double* const cl = ws.c + static_cast<int64_t>(l) * F * E;
+  family_tokens(D, F, L, E, k, l, inv_n, nf);
+  if (wave == 0) {
+    const double m = wave_max(lane < row_blocks ? sl[lane] : 0.0);  // at most E / 4 <= 64 row blocks
+    if (lane == 0) ws.max[l] = m;
+  }
+  __syncthreads();
+  // sums over the families of every expert, a quarter of the families per thread
+  const int e4 = tid & 255, part = tid >> 8;
+  if (e4 < E) {
+    double su = 0.0, scv = 0.0;
+#pragma unroll 4
+    for (int g = part; g < F; g += 4) {
+      const double n = nf[g];
+      su += n > 0 ? D[(static_cast<int64_t>(g) * L + l) * E + e4] / (n * k) : 0.0;
+      scv += cl[g * E + e4];
+    }
+    sum_u[part * E + e4] = su;
+    sum_c[part * E + e4] = scv;
+  }
+  __syncthreads();
+  // soft scores, a wave per family
+  for (int f = wave; f < F; f += kWaves) {
+    const double n = nf[f];
+    double du[4], dc[4], mu_u = 0.0, mu_c = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = lane + 64 * q;
+      du[q] = dc[q] = 0.0;
+      if (e < E) {
+        const double uf = n > 0 ? D[(static_cast<int64_t>(f) * L + l) * E + e] / (n * k) : 0.0;
+        const double cf = cl[f * E + e];
+        const double su = (sum_u[e] + sum_u[E + e]) + (sum_u[2 * E + e] + sum_u[3 * E + e]);
+        const double scv = (sum_c[e] + sum_c[E + e]) + (sum_c[2 * E + e] + sum_c[3 * E + e]);
+        du[q] = uf - (su - uf) / (F - 1);
+        dc[q] = cf - (scv - cf) / (F - 1);
+      }
+      mu_u += du[q];
+      mu_c += dc[q];
+    }
+    mu_u = wave_sum(mu_u) / E;
+    mu_c = wave_sum(mu_c) / E;
+    double vu = 0.0, vc = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (lane + 64 * q < E) {
+        vu += (du[q] - mu_u) * (du[q] - mu_u);
+        vc += (dc[q] - mu_c) * (dc[q] - mu_c);
+      }
+    }
+    const double su = sqrt(wave_sum(vu) / E) + eps, sv = sqrt(wave_sum(vc) / E) + eps;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = lane + 64 * q;
+      if (e < E) sc[f * E + e] = ((du[q] - mu_u) / su + (dc[q] - mu_c) / sv) / tau;
+    }
+  }
+  __syncthreads();
+  // softmax over the families: maximum, exponentials, denominator
+  if (tid < E) {
+    double m = -INFINITY;
+    for (int f = 0; f < F; ++f) m = fmax(m, sc[f * E + tid]);
+    sum_u[tid] = m;
+  }
+  __syncthreads();
+  for (int i = tid; i < F * E; i += kPrefThreads) sc[i] = exp(sc[i] - sum_u[i % E]);
+  __syncthreads();
+  if (tid < E) {
+    double d = 0.0;
+    for (int f = 0; f < F; ++f) d += sc[f * E + tid];
+    sum_c[tid] = d;
+  }
+  __syncthreads();
+  for (int i = tid; i < F * E; i += kPrefThreads) {
+    const int f = i / E, e = i - f * E;
+    const double p = sc[i] / sum_c[e];
+    sl[i] = p;
+    pref[(static_cast<int64_t>(l) * E + e) * F + f] = static_cast<float>(p);
+  }
+}
+
+__global__ __launch_bounds__(256, 4) void rw_graph(int F, int L, int E, double alpha, float* __restrict__ a_tilde,
+                                                   float* __restrict__ a_hat, RwWs ws) {
+  extern __shared__ __align__(16) double P[];  // [F][E] preferences of the layer
+  const int l = blockIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  static_assert(kRows == 16, "four rows per wave");
+  const int r0 = blockIdx.y * kRows + 4 * wave;
+  const double* sl = ws.s + static_cast<int64_t>(l) * F * E;
+  double ah[4][4];  // A-bar of this wave's rows, in flight while the preferences are staged
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      ah[r][q] = ws.abar[(static_cast<int64_t>(l) * E + min(r0 + r, E - 1)) * E + min(lane + 64 * q, E - 1)];
+  for (int i = threadIdx.x; i < F * E; i += blockDim.x) P[i] = sl[i];
+  __syncthreads();
+  const double mx = ws.max[l];
+  const double inv = mx > 0.0 ? 1.0 / mx : 0.0;
+  double task[4][4] = {};
+  for (int f = 0; f < F; ++f) {
+    double pi[4], pj[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) pi[r] = P[f * E + min(r0 + r, E - 1)];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) pj[q] = P[f * E + min(lane + 64 * q, E - 1)];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) task[r][q] += pi[r] * pj[q];
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if (r0 + r >= E) break;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int j = lane + 64 * q;
+      if (j >= E) continue;
+      const double h = mx > 0.0 ? ah[r][q] * inv : 0.0;
+      const int64_t o = (static_cast<int64_t>(l) * E + r0 + r) * E + j;
+      a_tilde[o] = static_cast<float>((1.0 - alpha) * h + alpha * (task[r][q] * h));
+      if (a_hat) a_hat[o] = static_cast<float>(h);
+    }
+  }
+}
+
+// GESR identification scores (Sec. 3.4, eq. generic-score) per row i of layer l, float64:
+// Cent = sum_j A-bar(i, j); Cons = mean_f cos(A_f(i, :), A-bar(i, :)) (0 for a zero row);
+// Spec = max_f ||A_f(i, :) - A-bar(i, :)||_2.  The waves share a row as in rw_rows: a wave keeps its eight families'
+// rows in registers between A-bar and the per-family terms, so C is read once.  Bound by the read of C and the
+// float64 arithmetic; measured on MI355X at E = 256, 16 families, 58 layers: 152 -> 70 us (C read twice, a wave sum per
+// family and term).  grid (L, row blocks); dynamic LDS: 2 x waves x E doubles.
+__global__ __launch_bounds__(512) void gesr_scores_kernel(const uint32_t* __restrict__ D, const uint32_t* __restrict__ C,
+                                                          int F, int L, int E, int k, int rows,
+                                                          double* __restrict__ cent, double* __restrict__ cons,
+                                                          double* __restrict__ spec) {
+  extern __shared__ double part[];  // [2][nw][E]
+  constexpr int kMaxWaves = TACG_MAX_FAMILIES / kSums;
+  __shared__ double row_cos[kRows][kMaxWaves], row_dev[kRows][kMaxWaves], row_sum[kRows];
+  const int l = blockIdx.x, nw = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r0 = blockIdx.y * rows, r1 = min(E, r0 + rows);
+  FamRows fr;
+  fr.init(D, C, F, L, E, k, l, kSums * wave);
+  fr.fetch(r0);
+  for (int i = r0; i < r1; ++i) {
+    uint32_t v[kSums][4];
+    fr.take(i, v);
+    fr.fetch(min(i + 1, E - 1));
+    double* const mine = part + static_cast<size_t>(((i & 1) * nw + wave)) * E;
+    double ab[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int u = 0; u < kSums; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) ab[q] += v[u][q] * fr.inv[u];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (lane + 64 * q < E) mine[lane + 64 * q] = ab[q];
+    __syncthreads();
+    const double* const all = part + static_cast<size_t>((i & 1) * nw) * E;
     double cs = 0.0, nb2 = 0.0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      ab[q] /= F;
+      ab[q] = 0.0;
+      if (lane + 64 * q < E) {
+        for (int w = 0; w < nw; ++w) ab[q] += all[w * E + lane + 64 * q];
+        ab[q] /= F;
+      }
       cs += ab[q];
       nb2 += ab[q] * ab[q];
     }
-    cs = wave_sum(cs);
-    nb2 = wave_sum(nb2);
-    const double nb = sqrt(nb2);
-    double cos_sum = 0.0, worst = 0.0;
-    for (int f0 = 0; f0 < F; f0 += kFamChunk) {
-      uint32_t v[kFamChunk][4];
-      load_rows(i, f0, v);
+    const double nb = sqrt(wave_sum(nb2));
+    double dot[kSums], na2[kSums], dev2[kSums];
 #pragma unroll
-      for (int u = 0; u < kFamChunk; ++u) {
-        const int f = f0 + u;
-        if (f >= F) break;
-        double dot = 0.0, na2 = 0.0, dev2 = 0.0;
+    for (int u = 0; u < kSums; ++u) {
+      dot[u] = na2[u] = dev2[u] = 0.0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int j = lane + 64 * q;
-          if (j < E) {
-            const double a = (j != i) ? v[u][q] * inv_n[f] : 0.0;
-            dot += a * ab[q];
-            na2 += a * a;
-            dev2 += (a - ab[q]) * (a - ab[q]);
-          }
-        }
-        dot = wave_sum(dot);
-        na2 = wave_sum(na2);
-        dev2 = wave_sum(dev2);
-        const double na = sqrt(na2);
-        cos_sum += (na > 0.0 && nb > 0.0) ? dot / (na * nb) : 0.0;
-        worst = fmax(worst, sqrt(dev2));
+      for (int q = 0; q < 4; ++q) {
+        __asm__ __volatile__("" : "+v"(v[u][q]));  // scaled again, not kept in 64-bit registers since A-bar
+        const double a = v[u][q] * fr.inv[u];
+        dot[u] += a * ab[q];
+        na2[u] += a * a;
+        dev2[u] += (a - ab[q]) * (a - ab[q]);
       }
     }
-    if (lane == 0) {
-      const int64_t o = static_cast<int64_t>(l) * E + i;
-      cent[o] = cs;
-      cons[o] = cos_sum / F;
-      spec[o] = worst;
+    // lane 8 u holds the sums of family u
+    const double d = wave_sum8(dot), n2 = wave_sum8(na2), e2 = wave_sum8(dev2);
+    const bool on = (lane >> 3) < fr.n;
+    const double na = sqrt(n2);
+    double cos_sum = (on && na > 0.0 && nb > 0.0) ? d / (na * nb) : 0.0;
+    double worst = on ? sqrt(e2) : 0.0;
+#pragma unroll
+    for (int o = 32; o >= 8; o >>= 1) {
+      cos_sum += __shfl_xor(cos_sum, o, 64);
+      worst = fmax(worst, __shfl_xor(worst, o, 64));
     }
+    if (wave == 0) cs = wave_sum(cs);
+    if (lane == 0) {
+      row_cos[i - r0][wave] = cos_sum;
+      row_dev[i - r0][wave] = worst;
+      if (wave == 0) row_sum[i - r0] = cs;
+    }
+  }
+  __syncthreads();
+  const int r = threadIdx.x;
+  if (r < r1 - r0) {
+    double c = 0.0, w = 0.0;
+    for (int u = 0; u < nw; ++u) {
+      c += row_cos[r][u];
+      w = fmax(w, row_dev[r][u]);
+    }
+    const int64_t o = static_cast<int64_t>(l) * E + r0 + r;
+    cent[o] = row_sum[r];
+    cons[o] = c / F;
+    spec[o] = w;
   }
 }
 
@@ -328,25 +444,38 @@ size_t reweight_workspace(int32_t F, int32_t L, int32_t E) {
   return used;
 }
 
+// Rows per workgroup of the row passes: about as many waves as the chip holds at three per SIMD, so that they run in
+// one round (16 rows left it at 1.8 waves per SIMD at 256 experts, 16 families, 58 layers; 8 rows made a round and a
+// quarter); at least four, so that N_f is not summed again for every few rows.
+static int rows_per_block(int L, int E, int nw) {
+  const int64_t waves = 3 * 4 * 256;
+  return static_cast<int>(std::max<int64_t>(4, std::min<int64_t>(kRows, (static_cast<int64_t>(L) * E * nw + waves - 1) / waves)));
+}
+
 int launch_reweight(const uint32_t* D, const uint32_t* C, int32_t F, int32_t L, int32_t E, int32_t k,
                     double alpha, double tau, double eps, float* pref, float* a_tilde, float* a_hat,
                     void* workspace, hipStream_t stream) {
   RwWs ws = carve_rw(workspace, F, L, E);
   const int rb = (E + kRows - 1) / kRows;
   const size_t plds = static_cast<size_t>(F) * E * sizeof(double);  // <= 64 x 256 x 8 = 128 KB
-  hipLaunchKernelGGL(rw_nf, dim3(L, F), dim3(64), 0, stream, D, F, L, E, k, ws);
-  hipLaunchKernelGGL(rw_rows, dim3(L, rb), dim3(256), 0, stream, C, F, L, E, ws);
-  hipLaunchKernelGGL(rw_z, dim3(L, F), dim3(256), 0, stream, D, F, L, E, k, tau, eps, ws);
+  const size_t slds = plds + 8 * static_cast<size_t>(E) * sizeof(double);
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&rw_pref), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            static_cast<int>(slds));
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&rw_graph), hipFuncAttributeMaxDynamicSharedMemorySize,
                             static_cast<int>(plds));
-  hipLaunchKernelGGL(rw_graph, dim3(L, rb), dim3(256), plds, stream, F, L, E, alpha, pref, a_tilde, a_hat, ws);
+  const int nw = (F + kSums - 1) / kSums, rows = rows_per_block(L, E, nw), blocks = (E + rows - 1) / rows;
+  hipLaunchKernelGGL(rw_rows, dim3(L, blocks), dim3(64 * nw), 2 * static_cast<size_t>(nw) * E * sizeof(double), stream, D,
+                     C, F, L, E, k, rows, ws);
+  hipLaunchKernelGGL(rw_pref, dim3(L), dim3(kPrefThreads), slds, stream, D, F, L, E, k, tau, eps, blocks, pref, ws);
+  hipLaunchKernelGGL(rw_graph, dim3(L, rb), dim3(256), plds, stream, F, L, E, alpha, a_tilde, a_hat, ws);
   return hipGetLastError() == hipSuccess ? TACG_OK : TACG_E_DEVICE;
 }
 
 int launch_gesr_scores(const uint32_t* D, const uint32_t* C, int32_t F, int32_t L, int32_t E, int32_t k, double* cent,
                        double* cons, double* spec, hipStream_t stream) {
-  hipLaunchKernelGGL(gesr_scores_kernel, dim3(L, (E + kRows - 1) / kRows), dim3(256), 0, stream, D, C, F, L, E, k,
-                     cent, cons, spec);
+  const int nw = (F + kSums - 1) / kSums, rows = rows_per_block(L, E, nw);
+  hipLaunchKernelGGL(gesr_scores_kernel, dim3(L, (E + rows - 1) / rows), dim3(64 * nw),
+                     2 * static_cast<size_t>(nw) * E * sizeof(double), stream, D, C, F, L, E, k, rows, cent, cons, spec);
   return hipGetLastError() == hipSuccess ? TACG_OK : TACG_E_DEVICE;
 }
 
