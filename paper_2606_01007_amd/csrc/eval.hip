@@ -10,9 +10,9 @@
 //                fallback GPU argmin_{m in FC} load_ref (ties: lowest number) and whether the expert
 //                has a single candidate in that placement
 //   ev_valid     validate the trace's ids: flag and count the token-layers with an id out of range
-//                or a repeated id, and mark their groups of 64 token-layers
-//   ev_main      the trace pass (below); also counts every expert's dispatches; an invalid token-layer
-//                (checked again only in marked groups) is not scored
+//                or a repeated id, and mark their groups of 64 token-layers; count every expert's dispatches
+//   ev_main      the trace pass (below); an invalid token-layer (checked again only in marked groups) is not scored.  At
+//                most 8 GPUs run on bit planes instead (eval_planes.hip), few placements with lane = token (eval_tokens.hip)
 //   ev_finalize  loads = counts of single-candidate experts on their primary + replicated choices;
 //                costs from the accumulators
 //
@@ -36,6 +36,10 @@ constexpr int kMainThreads = 1024;
 // when the families' ragged last pieces make the workgroups uneven (measured 2 % faster than 4096
 // on a Dirichlet family mix), long enough to amortise the table set-up and the flushes.
 constexpr int64_t kTargetWorkgroups = 8192;
+
+struct CountSegs {  // end token of every family
+  uint32_t end[TACG_MAX_FAMILIES];
+};
 
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void ev_zero(EvArgs a) {
@@ -62,57 +66,112 @@ __global__ __launch_bounds__(256) void ev_zero(EvArgs a) {
   }
 }
 
-// Trace validation (a1): every token-layer's ids, one wave per 64 consecutive token-layers of the
-// flattened trace (x = l * N + t), grid-stride.  A token-layer with an id out of range or a repeated id
-// is flagged, counted (n_bad) and marks its group of 64 in bad_tiles, so that ev_main checks the ids
-// itself only in the few tiles that meet a marked group.
+// Trace validation and dispatch counts: every token-layer's ids, read once.  A workgroup takes a contiguous range of the
+// flattened trace (x = l * N + t) and walks the layers (with statistics: the families of the layers) it crosses,
+// counting the dispatches of every expert in LDS.  A token-layer with an id out of range or a repeated id is flagged,
+// counted (n_bad), left out of the counts, and marks its group of 64 consecutive token-layers in bad_tiles, so that
+// ev_main checks the ids itself only in the few tiles that meet a marked group.
+// Bound by the read of the trace: the LDS adds of the counts hide behind it (2^19 tokens x 58 layers, top-8: 78 us
+// without them, and 100 us with them, while they cost the trace pass of few placements a fifth of its time).
 template <int K>
-__global__ __launch_bounds__(256) void ev_valid(EvArgs a) {
+__global__ __launch_bounds__(256) void ev_valid(EvArgs a, CountSegs segs) {
+  __shared__ uint32_t ecnt[TACG_MAX_EXPERTS];
   const int64_t total = a.N * a.L;
-  const int lane = threadIdx.x & 63;
-  const int64_t nwaves = static_cast<int64_t>(gridDim.x) * (blockDim.x >> 6);
+  const int tid = threadIdx.x, lane = tid & 63;
+  int64_t pos = total * blockIdx.x / gridDim.x;
+  const int64_t end = total * (blockIdx.x + 1) / gridDim.x;
+  const uint32_t E = static_cast<uint32_t>(a.E);
   uint32_t err = 0;
-  for (int64_t g = static_cast<int64_t>(blockIdx.x) * (blockDim.x >> 6) + (threadIdx.x >> 6); g * 64 < total;
-       g += nwaves) {
-    const int64_t x = g * 64 + lane;
-    bool bad = false;
-    if (x < total) {
-      const int16_t* idp = a.trace + x * K;
-      uint32_t raw[K];
+  for (int e = tid; e < a.E; e += blockDim.x) ecnt[e] = 0;
+  __syncthreads();
+  while (pos < end) {
+    const int64_t l = pos / a.N;
+    int f = 0;
+    int64_t stop = min(end, (l + 1) * a.N);
+    if (a.stats) {
+      const int64_t t = pos - l * a.N;
+      while (static_cast<int64_t>(segs.end[f]) <= t) ++f;
+      stop = min(end, l * a.N + static_cast<int64_t>(segs.end[f]));
+    }
+    const int64_t last = stop - 1;
+    constexpr int kAhead = 2;  // steps in flight behind the current one
+    TraceIds<K> ring[kAhead];
 #pragma unroll
-      for (int s = 0; s < K; ++s) raw[s] = static_cast<uint16_t>(idp[s]);
-      bool ok = true, dup = false;
+    for (int d = 0; d < kAhead; ++d) ring[d].fetch(a.trace + min(pos + tid + d * 256, last) * K);
+    for (int64_t xb = pos; xb < stop; xb += kAhead * 256) {
 #pragma unroll
-      for (int s = 0; s < K; ++s) {
-        ok &= raw[s] < static_cast<uint32_t>(a.E);
+      for (int d = 0; d < kAhead; ++d) {
+        const int64_t x = xb + d * 256 + tid;
+        uint32_t raw[K];
+        ring[d].unpack(raw);
+        ring[d].fetch(a.trace + min(x + kAhead * 256, last) * K);
+        const bool in = x < stop;
+        bool ok = true, dup = false;
 #pragma unroll
-        for (int q = 0; q < s; ++q) dup |= raw[s] == raw[q];
+        for (int s = 0; s < K; ++s) {
+          ok &= raw[s] < E;
+#pragma unroll
+          for (int q = 0; q < s; ++q) dup |= raw[s] == raw[q];
+        }
+        if (in && ok && !dup) {
+#pragma unroll
+          for (int s = 0; s < K; ++s)
+            __hip_atomic_fetch_add(&ecnt[raw[s]], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        const bool bad = in && (!ok || dup);
+        if (bad) {
+          err |= (ok ? 0u : TACG_ERR_ID_RANGE) | (dup ? TACG_ERR_ID_DUP : 0u);
+          atomicOr(&a.ws.bad_tiles[x >> 11], 1u << ((x >> 6) & 31));
+        }
+        const uint64_t b = __ballot(bad);
+        if (b != 0u && lane == 0) atomicAdd(a.ws.n_bad, static_cast<unsigned long long>(__popcll(b)));
       }
-      if (!ok) err |= TACG_ERR_ID_RANGE;
-      if (dup) err |= TACG_ERR_ID_DUP;
-      bad = !ok || dup;
     }
-    const uint64_t b = __builtin_amdgcn_ballot_w64(bad);
-    if (b != 0u && lane == 0) {
-      atomicOr(&a.ws.bad_tiles[g >> 5], 1u << (g & 31));
-      atomicAdd(a.ws.n_bad, static_cast<unsigned long long>(__builtin_popcountll(b)));
+    barrier_after_lds_atomics();
+    for (int e = tid; e < a.E; e += blockDim.x) {
+      const uint32_t c = ecnt[e];
+      if (c) {
+        atomicAdd(&a.ws.cnt[l * a.E + e], c);
+        if (a.stats) atomicAdd(&a.ws.cnt_fam[(static_cast<int64_t>(f) * a.L + l) * a.E + e], c);
+      }
+      ecnt[e] = 0;
     }
+    __syncthreads();
+    pos = stop;
   }
   if (err) atomicOr(a.d_err, err);
 }
 
-// Table validation and the replicated-expert marks.  Flat grid-stride loop over (p, l, e).
+// Table validation and the replicated-expert marks.  Flat grid-stride loop over (p, l, e), four experts of a thread
+// in flight (bound by the latency of the byte loads otherwise: 95 us at 1024 placements x 58 layers x 256 experts with three
+// secondaries, 61 us with four).
+constexpr int kFlagsAhead = 4;
+
+template <int R>
 __global__ __launch_bounds__(256) void ev_flags(EvArgs a) {
   const int64_t n = static_cast<int64_t>(a.P) * a.L * a.E;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
   uint32_t err = 0;
-  for (int64_t pe = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; pe < n;
-       pe += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    const uint8_t g0 = a.primary[pe];
+  for (int64_t pe0 = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; pe0 < n; pe0 += kFlagsAhead * stride) {
+   uint8_t prim[kFlagsAhead], sec[kFlagsAhead][R > 0 ? R : 1];
+#pragma unroll
+   for (int u = 0; u < kFlagsAhead; ++u) {
+    const int64_t pe = min(pe0 + u * stride, n - 1);
+    prim[u] = a.primary[pe];
+#pragma unroll
+    for (int r = 0; r < R; ++r) sec[u][r] = a.secondary[pe * R + r];
+   }
+#pragma unroll
+   for (int u = 0; u < kFlagsAhead; ++u) {
+    const int64_t pe = pe0 + u * stride;
+    if (pe >= n) break;
+    const uint8_t g0 = prim[u];
     if (g0 >= a.G) err |= TACG_ERR_TABLE;
     bool any = false;
     uint32_t seen = g0 < a.G ? (1u << g0) : 0u;
-    for (int r = 0; r < a.R; ++r) {
-      const uint8_t g = a.secondary[pe * a.R + r];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const uint8_t g = sec[u][r];
       if (g == kNone) continue;
       if (g >= a.G || (seen >> g) & 1u) {
         err |= TACG_ERR_TABLE;
@@ -130,6 +189,7 @@ __global__ __launch_bounds__(256) void ev_flags(EvArgs a) {
       const uint32_t bit = 1u << (e & 31);
       if (!(__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit)) atomicOr(w, bit);
     }
+   }
   }
   if (err) atomicOr(a.d_err, err);
 }
@@ -163,79 +223,89 @@ __global__ __launch_bounds__(256) void ev_replist(EvArgs a) {
   }
 }
 
-// Feasible candidates and fallback for every (placement, layer, replicated expert).
-// grid (ceil(P / 256), L), one thread per placement.
+// Feasible candidates and fallback for every (placement, layer, replicated expert).  A wave takes four placements of a
+// layer, sixteen lanes each: the lanes first hold the placement's loads (two GPUs per lane) for the guard, then one replicated
+// expert each.  grid (ceil(P / 16), L), 256 threads.  Bound by latency: one thread per placement working through its sixteen
+// experts took 34 us for two placements and 44 us for 1024 (58 layers, 32 GPUs, 16 experts with three secondaries); this takes
+// 5 and 19 us.
 __global__ __launch_bounds__(256) void ev_repinfo(EvArgs a) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x, l = blockIdx.y;
-  if (p >= a.P) return;
+  static_assert(TACG_MAX_REPLICATED == 16 && TACG_MAX_GPUS == 32, "sixteen lanes per placement");
+  __shared__ int64_t loads[16][TACG_MAX_GPUS];
+  const int l = blockIdx.y, lane = threadIdx.x & 63, i16 = lane & 15, local = threadIdx.x >> 4;
+  const int p = blockIdx.x * 16 + local, pc = min(p, a.P - 1);
   const int nrep = a.ws.n_rep[l];
   if (nrep == 0) return;
   const int G = a.G;
-  const int64_t* ref = a.load_ref + (static_cast<int64_t>(p) * a.L + l) * G;
-  // this placement's snapshot loads in registers (all loads in flight at once)
-  int64_t rf[TACG_MAX_GPUS];
+  const int64_t* ref = a.load_ref + (static_cast<int64_t>(pc) * a.L + l) * G;
+  int64_t v[2];
 #pragma unroll
-  for (int m = 0; m < TACG_MAX_GPUS; ++m) rf[m] = m < G ? ref[m] : 0;
-  // the candidate sets of the replicated experts, gathered before they are used
-  uint32_t cands[TACG_MAX_REPLICATED];
-#pragma unroll
-  for (int r = 0; r < TACG_MAX_REPLICATED; ++r) {
-    uint32_t cand = 0;
-    if (r < nrep) {
-      const int e = a.ws.rep_list[l * TACG_MAX_REPLICATED + r];
-      const int64_t pe = (static_cast<int64_t>(p) * a.L + l) * a.E + e;
-      const uint8_t g0 = a.primary[pe];
-      if (g0 < G) cand |= 1u << g0;
-      for (int q = 0; q < a.R; ++q) {
-        const uint8_t g = a.secondary[pe * a.R + q];
-        if (g < G) cand |= 1u << g;
-      }
+  for (int j = 0; j < 2; ++j) {
+    const int m = i16 + 16 * j;
+    v[j] = m < G ? ref[min(m, G - 1)] : 0;
+    loads[local][m] = v[j];
+  }
+  // this lane's expert: its candidate set
+  uint32_t cand = 0;
+  if (i16 < nrep) {
+    const int e = a.ws.rep_list[l * TACG_MAX_REPLICATED + i16];
+    const int64_t pe = (static_cast<int64_t>(pc) * a.L + l) * a.E + e;
+    const uint8_t g0 = a.primary[pe];
+    if (g0 < G) cand |= 1u << g0;
+    for (int q = 0; q < a.R; ++q) {
+      const uint8_t g = a.secondary[pe * a.R + q];
+      if (g < G) cand |= 1u << g;
     }
-    cands[r] = cand;
   }
   // eq. feasible-set with the mean load of eq. mean-load, exact in 128-bit integers
   uint32_t feas = (G == 32) ? 0xffffffffu : ((1u << G) - 1u);
   if (a.theta_den != 0) {
-    __int128 total = 0;
+    // the total as sums of the 32-bit halves over the sixteen lanes
+    int64_t hi = (v[0] >> 32) + (v[1] >> 32);
+    int64_t lo = (v[0] & 0xffffffffll) + (v[1] & 0xffffffffll);
 #pragma unroll
-    for (int m = 0; m < TACG_MAX_GPUS; ++m) total += rf[m];
+    for (int o = 8; o >= 1; o >>= 1) {
+      hi += __shfl_xor(hi, o, 64);
+      lo += __shfl_xor(lo, o, 64);
+    }
+    const __int128 total = static_cast<__int128>(hi) * (int64_t(1) << 32) + lo;
     const __int128 rhs = static_cast<__int128>(a.theta_den + a.theta_num) * total;
     feas = 0;
 #pragma unroll
-    for (int m = 0; m < TACG_MAX_GPUS; ++m)
-      if (m < G && static_cast<__int128>(a.theta_den) * G * rf[m] <= rhs) feas |= 1u << m;
-  }
-#pragma unroll
-  for (int r = 0; r < TACG_MAX_REPLICATED; ++r) {
-    if (r >= nrep) break;
-    uint32_t cand = cands[r];
-    if (cand == 0) cand = 1u;  // invalid table (already flagged): keep the choice in range
-    uint32_t fc = cand & feas;
-    if (fc == 0) fc = cand;
-    // least-loaded feasible candidate, ties to the lowest GPU
-    int best = -1;
-    int64_t bestv = 0;
-#pragma unroll
-    for (int m = 0; m < TACG_MAX_GPUS; ++m) {
-      if (((fc >> m) & 1u) && (best < 0 || rf[m] < bestv)) {
-        best = m;
-        bestv = rf[m];
-      }
+    for (int j = 0; j < 2; ++j) {
+      const bool ok = i16 + 16 * j < G && static_cast<__int128>(a.theta_den) * G * v[j] <= rhs;
+      const uint64_t bal = __ballot(ok);
+      feas |= (static_cast<uint32_t>(bal >> (lane & 48)) & 0xffffu) << (16 * j);
     }
-    // bit 31: the expert has a single candidate in this placement (it is served by its primary and
-    // belongs to the GPUs the token reaches before any multi-candidate slot is resolved)
-    const uint32_t single = (__popc(cand) == 1) ? 0x80000000u : 0u;
-    a.ws.rep_info[(static_cast<int64_t>(l) * TACG_MAX_REPLICATED + r) * a.P + p] =
-        make_uint2(fc, static_cast<uint32_t>(best) | single);
   }
+  if (p >= a.P || i16 >= nrep) return;
+  // the loads were staged by lanes of this wave: the LDS keeps its operations in order
+  __asm__ __volatile__("" ::: "memory");
+  if (cand == 0) cand = 1u;  // invalid table (already flagged): keep the choice in range
+  uint32_t fc = cand & feas;
+  if (fc == 0) fc = cand;
+  // least-loaded feasible candidate, ties to the lowest GPU
+  int best = __builtin_ctz(fc);
+  int64_t bestv = loads[local][best];
+  for (uint32_t rest = fc & (fc - 1u); rest != 0u; rest &= rest - 1u) {
+    const int m = __builtin_ctz(rest);
+    const int64_t x = loads[local][m];
+    if (x < bestv) {
+      best = m;
+      bestv = x;
+    }
+  }
+  // bit 31: the expert has a single candidate in this placement (it is served by its primary and
+  // belongs to the GPUs the token reaches before any multi-candidate slot is resolved)
+  const uint32_t single = (__popc(cand) == 1) ? 0x80000000u : 0u;
+  a.ws.rep_info[(static_cast<int64_t>(l) * TACG_MAX_REPLICATED + i16) * a.P + p] =
+      make_uint2(fc, static_cast<uint32_t>(best) | single);
 }
 
 // ------------------------------------------------------------------------------------------------
 // The trace pass.  PPL placements per lane (one 8- or 16-byte LDS read per slot serves all of them);
 // a workgroup scores 64 * PPL placements of one layer on one piece of one family's tokens.
-// grid (placement blocks, pieces, L).  The workgroups of placement block 0 also count the
-// dispatches of every expert (each token-layer is seen by exactly one of them); ev_valid has already
-// checked the ids, and only tiles it marked check them again, to leave their invalid token-layers out.
+// grid (placement blocks, pieces, L).  ev_valid has already checked the ids, and only tiles it marked check them
+// again, to leave their invalid token-layers out.
 // Choices for replicated experts are counted in 16-bit LDS counters (two per dword).  After every
 // round of at most 65535 / K tokens (so that they cannot overflow) each thread adds a fixed set of
 // them into 32-bit registers and clears them; the registers go to the workspace once per workgroup.
@@ -375,8 +445,7 @@ struct Scorer {
 // fallback choices are packed per band position.
 template <int K, int PPL, bool NARROW, bool STATS, bool CHECK>
 __device__ __forceinline__ void score_piece(const EvArgs& a, const uint32_t* tbl, const uint2* rinfo, uint32_t* rcnt,
-                                            uint32_t* ecnt, const uint8_t* rep_of, int l, int p0, int nrep,
-                                            bool counter, uint32_t t_begin, uint32_t t_end, uint32_t off_f,
+                                            const uint8_t* rep_of, int l, int p0, int nrep, uint32_t t_begin, uint32_t t_end, uint32_t off_f,
                                             uint32_t hs, uint32_t hz, int f,
                                             uint32_t (&acc_span)[PPL], uint32_t (&acc_home)[PPL],
                                             uint32_t (&acc_cross)[PPL], uint32_t& n_scored) {
@@ -456,11 +525,6 @@ __device__ __forceinline__ void score_piece(const EvArgs& a, const uint32_t* tbl
           }
           bad = !ok || dup;
           if (bad) info = IL::kBad;
-        }
-        if (counter && !bad) {
-#pragma unroll
-          for (int s = 0; s < K; ++s)
-            __hip_atomic_fetch_add(&ecnt[raw[s]], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
       }
       const uint32_t ntile = min(64u, r_end - tile);
@@ -562,12 +626,10 @@ __global__ __launch_bounds__(kMainThreads) void ev_main(EvArgs a) {
   const int piece = tile % a.n_pieces, l = tile / a.n_pieces;
   const int p0 = pb * PW;
   const int nrep = a.ws.n_rep[l];
-  const bool counter = (pb == 0);
   uint32_t* tbl = lds;                                                // [E][PW] one-hot GPU masks
   uint2* rinfo = reinterpret_cast<uint2*>(lds + E * PW);              // [MAX_REP][PW] (FC, fallback)
   uint32_t* rcnt = lds + E * PW + 2 * TACG_MAX_REPLICATED * PW;       // [G][PW / 2] two u16 counters
-  uint32_t* ecnt = rcnt + G * PW / 2;                                 // [E] dispatch counts
-  uint8_t* rep_of = reinterpret_cast<uint8_t*>(ecnt + E);             // [E]
+  uint8_t* rep_of = reinterpret_cast<uint8_t*>(rcnt + G * PW / 2);    // [E]
   // [kRed][PW] per-placement cost sums of the workgroup's waves, then the sum of their n_scored
   constexpr int kRed = STATS ? 3 : 2;  // span, home (and cross)
   uint32_t* red = reinterpret_cast<uint32_t*>(rep_of + ((E + 255) & ~255));  // rep_of padded to 256 bytes
@@ -612,10 +674,7 @@ __global__ __launch_bounds__(kMainThreads) void ev_main(EvArgs a) {
   }
   for (int i = threadIdx.x; i < G * PW / 2; i += blockDim.x) rcnt[i] = 0;
   for (int i = threadIdx.x; i < kRed * PW + 1; i += blockDim.x) red[i] = 0;
-  for (int i = threadIdx.x; i < E; i += blockDim.x) {
-    rep_of[i] = rep_of_g[i];
-    ecnt[i] = 0;
-  }
+  for (int i = threadIdx.x; i < E; i += blockDim.x) rep_of[i] = rep_of_g[i];
   __syncthreads();
 
   const int lane = threadIdx.x & 63;
@@ -626,17 +685,17 @@ __global__ __launch_bounds__(kMainThreads) void ev_main(EvArgs a) {
   uint32_t n_scored = 0;  // token-layers scored by this wave
   if (any_bad) {  // a trace with invalid token-layers: the variant that checks the marked tiles
     if (hz <= 4) {
-      score_piece<K, PPL, true, STATS, true>(a, tbl, rinfo, rcnt, ecnt, rep_of, l, p0, nrep, counter, t_begin, t_end,
+      score_piece<K, PPL, true, STATS, true>(a, tbl, rinfo, rcnt, rep_of, l, p0, nrep, t_begin, t_end,
                                              off_f, hs, hz, f, acc_span, acc_home, acc_cross, n_scored);
     } else {
-      score_piece<K, PPL, false, STATS, true>(a, tbl, rinfo, rcnt, ecnt, rep_of, l, p0, nrep, counter, t_begin, t_end,
+      score_piece<K, PPL, false, STATS, true>(a, tbl, rinfo, rcnt, rep_of, l, p0, nrep, t_begin, t_end,
                                               off_f, hs, hz, f, acc_span, acc_home, acc_cross, n_scored);
     }
   } else if (hz <= 4) {
-    score_piece<K, PPL, true, STATS, false>(a, tbl, rinfo, rcnt, ecnt, rep_of, l, p0, nrep, counter, t_begin, t_end,
+    score_piece<K, PPL, true, STATS, false>(a, tbl, rinfo, rcnt, rep_of, l, p0, nrep, t_begin, t_end,
                                             off_f, hs, hz, f, acc_span, acc_home, acc_cross, n_scored);
   } else {
-    score_piece<K, PPL, false, STATS, false>(a, tbl, rinfo, rcnt, ecnt, rep_of, l, p0, nrep, counter, t_begin, t_end,
+    score_piece<K, PPL, false, STATS, false>(a, tbl, rinfo, rcnt, rep_of, l, p0, nrep, t_begin, t_end,
                                              off_f, hs, hz, f, acc_span, acc_home, acc_cross, n_scored);
   }
 
@@ -672,56 +731,73 @@ __global__ __launch_bounds__(kMainThreads) void ev_main(EvArgs a) {
       }
     }
   }
-  if (counter) {
-    barrier_after_lds_atomics();
-    for (int i = threadIdx.x; i < E; i += blockDim.x) {
-      if (ecnt[i]) {
-        atomicAdd(&a.ws.cnt[static_cast<int64_t>(l) * E + i], ecnt[i]);
-        if constexpr (STATS) atomicAdd(&a.ws.cnt_fam[(static_cast<int64_t>(f) * L + l) * E + i], ecnt[i]);
-      }
-    }
-  }
 }
 
-// loads and costs.  grid (P, L), 256 threads.
-__global__ __launch_bounds__(256) void ev_finalize(EvArgs a, uint64_t* __restrict__ cost_home,
-                                                   uint64_t* __restrict__ cost_span, uint32_t* __restrict__ load,
-                                                   uint64_t* __restrict__ cost_home_fam) {
-  __shared__ uint32_t acc[TACG_MAX_GPUS];
-  const int p = blockIdx.x, l = blockIdx.y;
+// Loads and costs.  A workgroup takes one layer and kLoadRun placements, a wave one placement at a time, as
+// placement_load_kernel.  grid (ceil(P / kLoadRun), L).
+constexpr int kLoadWaves = 8;
+constexpr int kLoadRun = 64;  // placements per workgroup
+
+__global__ __launch_bounds__(64 * kLoadWaves) void ev_finalize(EvArgs a, uint64_t* __restrict__ cost_home,
+                                                               uint64_t* __restrict__ cost_span,
+                                                               uint32_t* __restrict__ load,
+                                                               uint64_t* __restrict__ cost_home_fam) {
+  __shared__ uint32_t acc[kLoadWaves][TACG_MAX_GPUS];
+  const int l = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int E = a.E, G = a.G, L = a.L;
-  if (threadIdx.x < G) acc[threadIdx.x] = 0;
-  __syncthreads();
-  for (int e = threadIdx.x; e < E; e += blockDim.x) {
-    if (a.ws.rep_of[static_cast<int64_t>(l) * E + e] != kNone) continue;
-    const uint8_t g = a.primary[(static_cast<int64_t>(p) * L + l) * E + e];
-    const uint32_t c = a.ws.cnt[static_cast<int64_t>(l) * E + e];
-    if (g < G && c) atomicAdd(&acc[g], c);
+  // dispatches of the experts that are served by their primary in every placement (a replicated one's are its choices)
+  uint32_t d[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int e = lane + 64 * q;
+    const int64_t le = static_cast<int64_t>(l) * E + min(e, E - 1);
+    d[q] = e < E && a.ws.rep_of[le] == kNone ? a.ws.cnt[le] : 0u;
   }
-  barrier_after_lds_atomics();
-  if (threadIdx.x < G) {
-    const int64_t o = (static_cast<int64_t>(p) * L + l) * G + threadIdx.x;
-    load[o] = acc[threadIdx.x] + a.ws.rep_load[(static_cast<int64_t>(l) * G + threadIdx.x) * even_up(a.P) + p];
-  }
-  if (l == 0) {
-    if (threadIdx.x == 0) {
-      cost_home[p] = a.ws.acc_home[p];
-      // |cards| - 1 per scored token-layer (every scored token-layer has at least one card)
-      cost_span[p] = a.ws.acc_span[p] - (static_cast<uint64_t>(a.N) * static_cast<uint64_t>(L) - *a.ws.n_bad);
+  const int p1 = min(a.P, static_cast<int>(blockIdx.x + 1) * kLoadRun);
+  uint8_t next[4];
+  uint32_t next_rep = 0;
+  auto fetch = [&](int p) {
+    const int pc = min(p, a.P - 1);
+    const uint8_t* src = a.primary + (static_cast<int64_t>(pc) * L + l) * E;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) next[q] = src[min(lane + 64 * q, E - 1)];
+    next_rep = a.ws.rep_load[(static_cast<int64_t>(l) * G + min(lane, G - 1)) * even_up(a.P) + pc];
+  };
+  int p = blockIdx.x * kLoadRun + wave;
+  fetch(p);
+  for (; p < p1; p += kLoadWaves) {
+    uint32_t g[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) g[q] = next[q];
+    const uint32_t rep = next_rep;
+    fetch(p + kLoadWaves);
+    if (lane < G) acc[wave][lane] = rep;
+    __asm__ __volatile__("" ::: "memory");  // the LDS keeps a wave's operations in order
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (d[q] && g[q] < static_cast<uint32_t>(G))
+        __hip_atomic_fetch_add(&acc[wave][g[q]], d[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __asm__ __volatile__("" ::: "memory");
+    if (lane < G) load[(static_cast<int64_t>(p) * L + l) * G + lane] = acc[wave][lane];
+    if (l == 0) {
+      if (lane == 0) {
+        cost_home[p] = a.ws.acc_home[p];
+        // |cards| - 1 per scored token-layer (every scored token-layer has at least one card)
+        cost_span[p] = a.ws.acc_span[p] - (static_cast<uint64_t>(a.N) * static_cast<uint64_t>(L) - *a.ws.n_bad);
+      }
+      if (cost_home_fam && lane < a.F)
+        cost_home_fam[static_cast<int64_t>(p) * a.F + lane] = a.ws.acc_fam[static_cast<int64_t>(lane) * a.P + p];
     }
-    if (cost_home_fam)
-      for (int f = threadIdx.x; f < a.F; f += blockDim.x)
-        cost_home_fam[static_cast<int64_t>(p) * a.F + f] = a.ws.acc_fam[static_cast<int64_t>(f) * a.P + p];
   }
 }
 
 // App. C statistics per (placement, family): home-family dispatch mass = dispatches of the family's
 // tokens to single-candidate experts whose primary lies in the family's band (from the per-family
 // dispatch counts) + replicated-slot choices inside the band (counted by ev_main).
-// grid (P, F), 256 threads.
-__global__ __launch_bounds__(256) void ev_stats(EvArgs a, uint64_t* __restrict__ span_fam,
+// grid (P, F), 1024 threads.
+__global__ __launch_bounds__(1024) void ev_stats(EvArgs a, uint64_t* __restrict__ span_fam,
                                                 uint64_t* __restrict__ cross_fam, uint64_t* __restrict__ hmass_fam) {
-  __shared__ unsigned long long red[4];
+  __shared__ unsigned long long red[16];
   const int p = blockIdx.x, f = blockIdx.y;
   const int E = a.E, L = a.L;
   const uint4 r = a.band4[f >> 2];
@@ -729,11 +805,11 @@ __global__ __launch_bounds__(256) void ev_stats(EvArgs a, uint64_t* __restrict__
   const uint32_t hs = bw & 0xffu, hz = (bw >> 8) & 0xffu;
   unsigned long long s = 0;
   const int64_t n = static_cast<int64_t>(L) * E;
-  for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-    if (a.ws.rep_of[i] != kNone) continue;
+#pragma unroll 4
+  for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {  // (l, e) flattened
     const uint32_t g = a.primary[static_cast<int64_t>(p) * n + i];
-    const int64_t le = i;  // (l, e) flattened
-    if (g - hs < hz) s += a.ws.cnt_fam[static_cast<int64_t>(f) * n + le];
+    const uint32_t c = a.ws.cnt_fam[static_cast<int64_t>(f) * n + i];
+    s += (a.ws.rep_of[i] == kNone && g - hs < hz) ? c : 0u;
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
@@ -741,7 +817,9 @@ __global__ __launch_bounds__(256) void ev_stats(EvArgs a, uint64_t* __restrict__
   __syncthreads();
   if (threadIdx.x == 0) {
     const int64_t pf = static_cast<int64_t>(p) * a.F + f, fp = static_cast<int64_t>(f) * a.P + p;
-    hmass_fam[pf] = red[0] + red[1] + red[2] + red[3] + a.ws.acc_hmass_fam[fp];
+    unsigned long long t = 0;
+    for (int w = 0; w < 16; ++w) t += red[w];
+    hmass_fam[pf] = t + a.ws.acc_hmass_fam[fp];
     span_fam[pf] = a.ws.acc_span_fam[fp];
     cross_fam[pf] = a.ws.acc_cross_fam[fp];
   }
@@ -752,7 +830,7 @@ int launch_main(const EvArgs& a, int n_pblocks, hipStream_t stream) {
   constexpr int PW = 64 * PPL;
   constexpr int kRed = STATS ? 3 : 2;
   const size_t lds = static_cast<size_t>(a.E) * PW * 4 + static_cast<size_t>(2) * TACG_MAX_REPLICATED * PW * 4 +
-                     static_cast<size_t>(a.G) * PW * 2 + static_cast<size_t>(a.E) * 4 + align256(a.E) +
+                     static_cast<size_t>(a.G) * PW * 2 + align256(a.E) +
                      static_cast<size_t>(kRed * PW + 1) * 4;
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&ev_main<K, PPL, STATS>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
@@ -766,10 +844,10 @@ int launch_main(const EvArgs& a, int n_pblocks, hipStream_t stream) {
 }
 
 template <int K>
-void launch_valid(const EvArgs& a, hipStream_t stream) {
-  const int64_t groups = (a.N * a.L + 63) / 64;  // one wave per 64 token-layers, four waves per block
-  const int blocks = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(8192, (groups + 3) / 4)));
-  hipLaunchKernelGGL(ev_valid<K>, dim3(blocks), dim3(256), 0, stream, a);
+void launch_valid(const EvArgs& a, const CountSegs& segs, hipStream_t stream) {
+  // eight workgroups per CU; fewer when a workgroup would see less than 2048 token-layers (its counts are flushed once)
+  const int blocks = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(2048, a.N * a.L / 2048)));
+  hipLaunchKernelGGL(ev_valid<K>, dim3(blocks), dim3(256), 0, stream, a, segs);
 }
 
 template <int K>
@@ -786,9 +864,6 @@ int launch_main_k(const EvArgs& a, hipStream_t stream) {
 // placement, the next placement's in flight) and by LDS adds on few addresses.  Measured on MI355X at E = 256, 32
 // GPUs, 16 families, 1024 placements x 58 layers: 140 -> 19 us (one workgroup per (placement, layer)
 // summed the families again each time).
-constexpr int kLoadWaves = 8;
-constexpr int kLoadRun = 64;  // placements per workgroup
-
 __global__ __launch_bounds__(64 * kLoadWaves) void placement_load_kernel(const uint32_t* __restrict__ D, int F, int L,
                                                                          int E, const uint8_t* __restrict__ primary,
                                                                          int P, int G, int64_t* __restrict__ load_ref,
@@ -844,12 +919,15 @@ __global__ __launch_bounds__(64) void jain_kernel(const uint32_t* __restrict__ l
   const int row = blockIdx.x;  // p (global) or p * L + l (per layer)
   const int m = threadIdx.x;
   uint64_t x = 0;
-  if (m < G) {
-    if (per_layer) {
-      x = load[static_cast<int64_t>(row) * G + m];
-    } else {
-      for (int l = 0; l < L; ++l) x += load[(static_cast<int64_t>(row) * L + l) * G + m];
-    }
+  if (per_layer) {
+    if (m < G) x = load[static_cast<int64_t>(row) * G + m];
+  } else {
+    // the two halves of the wave take the even and the odd layers (G <= 32), several loads in flight
+    const int c = min(m & 31, G - 1);
+#pragma unroll 8
+    for (int l = m >> 5; l < L; l += 2) x += load[(static_cast<int64_t>(row) * L + l) * G + c];
+    x += __shfl_xor(x, 32, 64);
+    if (m >= G) x = 0;
   }
   // exact integer sums; the square sum is formed in float64 (it can exceed 64 bits)
   uint64_t s = x, mx = x;
@@ -946,21 +1024,33 @@ int launch_eval(const int16_t* trace, int64_t N, int32_t L, int32_t K, int32_t E
   hipLaunchKernelGGL(ev_zero, dim3(256), dim3(256), 0, stream, a);
   {
     const int64_t n = static_cast<int64_t>(P) * L * E;
-    const int blocks = static_cast<int>(std::min<int64_t>(2048, (n + 255) / 256));
-    hipLaunchKernelGGL(ev_flags, dim3(blocks), dim3(256), 0, stream, a);
+    const int blocks = static_cast<int>(std::min<int64_t>(2048, (n + 256 * kFlagsAhead - 1) / (256 * kFlagsAhead)));
+const dim3 grid(blocks), block(256);
+    switch (R) {
+      case 0: hipLaunchKernelGGL(ev_flags<0>, grid, block, 0, stream, a); break;
+      case 1: hipLaunchKernelGGL(ev_flags<1>, grid, block, 0, stream, a); break;
+      case 2: hipLaunchKernelGGL(ev_flags<2>, grid, block, 0, stream, a); break;
+      case 3: hipLaunchKernelGGL(ev_flags<3>, grid, block, 0, stream, a); break;
+      default: hipLaunchKernelGGL(ev_flags<4>, grid, block, 0, stream, a); break;
+    }
   }
   hipLaunchKernelGGL(ev_replist, dim3(L), dim3(256), 0, stream, a);
-  if (R > 0) hipLaunchKernelGGL(ev_repinfo, dim3((P + 255) / 256, L), dim3(256), 0, stream, a);
+  if (R > 0) hipLaunchKernelGGL(ev_repinfo, dim3((P + 15) / 16, L), dim3(256), 0, stream, a);
   if (hipGetLastError() != hipSuccess) return TACG_E_DEVICE;
   if (np > 0) {
     const bool planes = stats == nullptr && eval_uses_planes(K, E, G);
+    const bool tokens = P <= kFewPlacements;
+    CountSegs segs;
+    for (int f = 0; f < TACG_MAX_FAMILIES; ++f)
+      segs.end[f] = f < F ? static_cast<uint32_t>(fam_off_host[f + 1]) : 0xffffffffu;
     int rc;
     switch (K) {
 #define TACG_K(k) \
   case k:         \
-    launch_valid<k>(a, stream);  \
-    rc = planes ? launch_eval_planes(a, fam_off_host, home_start_host, home_size_host, stream) \
-                : launch_main_k<k>(a, stream); \
+    launch_valid<k>(a, segs, stream);  \
+    rc = planes   ? launch_eval_planes(a, fam_off_host, home_start_host, home_size_host, stream) \
+         : tokens ? launch_eval_tokens(a, fam_off_host, home_start_host, home_size_host, stream) \
+                  : launch_main_k<k>(a, stream); \
     break;
       TACG_K(1) TACG_K(2) TACG_K(3) TACG_K(4) TACG_K(5) TACG_K(6) TACG_K(7) TACG_K(8)
       TACG_K(9) TACG_K(10) TACG_K(11) TACG_K(12) TACG_K(13) TACG_K(14) TACG_K(15) TACG_K(16)
@@ -971,9 +1061,10 @@ int launch_eval(const int16_t* trace, int64_t N, int32_t L, int32_t K, int32_t E
     if (rc != TACG_OK) return rc;
     if (hipGetLastError() != hipSuccess) return TACG_E_DEVICE;
   }
-  hipLaunchKernelGGL(ev_finalize, dim3(P, L), dim3(256), 0, stream, a, cost_home, cost_span, load, cost_home_fam);
+  hipLaunchKernelGGL(ev_finalize, dim3((P + kLoadRun - 1) / kLoadRun, L), dim3(64 * kLoadWaves), 0, stream, a, cost_home,
+                     cost_span, load, cost_home_fam);
   if (stats != nullptr)
-    hipLaunchKernelGGL(ev_stats, dim3(P, F), dim3(256), 0, stream, a, stats->span_fam, stats->cross_fam,
+    hipLaunchKernelGGL(ev_stats, dim3(P, F), dim3(1024), 0, stream, a, stats->span_fam, stats->cross_fam,
                        stats->home_mass_fam);
   return hipGetLastError() == hipSuccess ? TACG_OK : TACG_E_DEVICE;
 }

@@ -1,4 +1,4 @@
-// Declarations shared by the placement-scoring kernels (eval.hip, eval_planes.hip): the workspace layout and
+// Declarations shared by the placement-scoring kernels (eval.hip, eval_planes.hip, eval_tokens.hip): the workspace layout and
 // the arguments of the passes around the trace pass.
 #pragma once
 
@@ -83,9 +83,50 @@ struct EvArgs {
 };
 static_assert(sizeof(EvArgs) <= 4096, "kernel arguments must stay within 4 KB");
 
+// The K int16 ids of a token-layer, fetched with the widest loads their alignment allows.
+template <int K>
+struct TraceIds {
+  static constexpr int kWords = K % 2 == 0 ? K / 2 : K;
+  uint32_t w[kWords];
+  __device__ __forceinline__ void fetch(const int16_t* p) {
+    if constexpr (K % 8 == 0) {
+#pragma unroll
+      for (int q = 0; q < K / 8; ++q) {
+        const uint4 v = reinterpret_cast<const uint4*>(p)[q];
+        w[4 * q] = v.x;
+        w[4 * q + 1] = v.y;
+        w[4 * q + 2] = v.z;
+        w[4 * q + 3] = v.w;
+      }
+    } else if constexpr (K % 4 == 0) {
+#pragma unroll
+      for (int q = 0; q < K / 4; ++q) {
+        const uint2 v = reinterpret_cast<const uint2*>(p)[q];
+        w[2 * q] = v.x;
+        w[2 * q + 1] = v.y;
+      }
+    } else if constexpr (K % 2 == 0) {
+#pragma unroll
+      for (int q = 0; q < K / 2; ++q) w[q] = reinterpret_cast<const uint32_t*>(p)[q];
+    } else {
+#pragma unroll
+      for (int s = 0; s < K; ++s) w[s] = static_cast<uint16_t>(p[s]);
+    }
+  }
+  __device__ __forceinline__ void unpack(uint32_t (&raw)[K]) const {
+#pragma unroll
+    for (int s = 0; s < K; ++s) raw[s] = K % 2 == 0 ? (w[s / 2] >> (16 * (s & 1))) & 0xffffu : w[K % 2 == 0 ? 0 : s];
+  }
+};
+
 // The bit-plane trace pass (eval_planes.hip): whether it takes these sizes, and its launch.
 bool eval_uses_planes(int32_t top_k, int32_t n_experts, int32_t n_gpus);
 int launch_eval_planes(const EvArgs& e, const int64_t* fam_off_host, const int32_t* home_start_host,
+                       const int32_t* home_size_host, hipStream_t stream);
+
+// The lane = token trace pass (eval_tokens.hip) for at most kFewPlacements placements, also with the App. C statistics.
+constexpr int32_t kFewPlacements = 24;
+int launch_eval_tokens(const EvArgs& e, const int64_t* fam_off_host, const int32_t* home_start_host,
                        const int32_t* home_size_host, hipStream_t stream);
 
 }  // namespace tacg

@@ -194,42 +194,6 @@ __device__ __forceinline__ void load_planes(uint32_t off, uint32_t (&v)[NP]) {
   }
 }
 
-// The K int16 ids of a token-layer, fetched with the widest loads their alignment allows.
-template <int K>
-struct Ids {
-  static constexpr int kWords = K % 2 == 0 ? K / 2 : K;
-  uint32_t w[kWords];
-  __device__ __forceinline__ void fetch(const int16_t* p) {
-    if constexpr (K % 8 == 0) {
-#pragma unroll
-      for (int q = 0; q < K / 8; ++q) {
-        const u32x4 v = reinterpret_cast<const u32x4*>(p)[q];
-        w[4 * q] = v.x;
-        w[4 * q + 1] = v.y;
-        w[4 * q + 2] = v.z;
-        w[4 * q + 3] = v.w;
-      }
-    } else if constexpr (K % 4 == 0) {
-#pragma unroll
-      for (int q = 0; q < K / 4; ++q) {
-        const u32x2 v = reinterpret_cast<const u32x2*>(p)[q];
-        w[2 * q] = v.x;
-        w[2 * q + 1] = v.y;
-      }
-    } else if constexpr (K % 2 == 0) {
-#pragma unroll
-      for (int q = 0; q < K / 2; ++q) w[q] = reinterpret_cast<const uint32_t*>(p)[q];
-    } else {
-#pragma unroll
-      for (int s = 0; s < K; ++s) w[s] = static_cast<uint16_t>(p[s]);
-    }
-  }
-  __device__ __forceinline__ void unpack(uint32_t (&raw)[K]) const {
-#pragma unroll
-    for (int s = 0; s < K; ++s) raw[s] = K % 2 == 0 ? (w[s / 2] >> (16 * (s & 1))) & 0xffffu : w[K % 2 == 0 ? 0 : s];
-  }
-};
-
 template <int K, int NP>
 struct PlLayout {
   static constexpr int NQ = NP / 4;                    // 256-byte rows per expert
@@ -244,7 +208,7 @@ struct PlLayout {
   static size_t bytes(int E, int threads) {
     size_t b = static_cast<size_t>(desc_off(E)) + static_cast<size_t>(threads) * DW * 4;
     b = std::max(b, static_cast<size_t>(kRed) * 4);
-    return b + 256 + static_cast<size_t>(E) * 4;  // rep_of, dispatch counts
+    return b + 256;  // rep_of
   }
   static int threads(int E) { return bytes(E, kThreads) <= kLdsMax ? kThreads : kThreadsSmall; }
 };
@@ -285,16 +249,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))
   size_t tail_off = tbl_end + static_cast<size_t>(nthreads) * DW * 4;
   if (tail_off < static_cast<size_t>(Lay::kRed) * 4) tail_off = static_cast<size_t>(Lay::kRed) * 4;
   uint8_t* const rep_of = reinterpret_cast<uint8_t*>(lds + tail_off);
-  uint32_t* const ecnt = reinterpret_cast<uint32_t*>(lds + tail_off + 256);
   const uint8_t* rep_of_g = a.ws.rep_of + static_cast<int64_t>(l) * E;
   const int nrep = a.ws.n_rep[l];
-  const bool counter = pb == 0;
 
   // ---- tables ----
-  for (int e = tid; e < E; e += nthreads) {
-    rep_of[e] = rep_of_g[e];
-    ecnt[e] = 0;
-  }
+  for (int e = tid; e < E; e += nthreads) rep_of[e] = rep_of_g[e];
   for (int i = tid; i < NQ * kRowB / 4; i += nthreads) reinterpret_cast<uint32_t*>(tbl + E * NQ * kRowB)[i] = 0;
   for (int i = tid; i < RS * kRowB / 4; i += nthreads)
     reinterpret_cast<uint32_t*>(rep + Lay::kNull * kRowB)[i] = 0;
@@ -428,7 +387,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))
     uint32_t n_step = 0;  // pushes so far (wave-uniform)
     const int16_t* trace_c = a.trace + (static_cast<int64_t>(l) * a.N + fr.off + pos) * K;
     const uint32_t ntile = (c1 - c0 + 63) / 64;
-    Ids<K> next;  // the ids of the wave's next tile, in flight while the current one is scored
+    TraceIds<K> next;  // the ids of the wave's next tile, in flight while the current one is scored
     next.fetch(trace_c + static_cast<int64_t>(min(c0 + first * 64 + lane, c1 - 1)) * hz * K);
     __syncthreads();  // the tables are in place
     for (uint32_t tile = first; tile < ntile; tile += nwaves) {
@@ -468,8 +427,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))
           for (int i = 0; i < KR; ++i) d[KW + i] ^= (static_cast<int>(cnt >> 2) == i) ? x : 0u;
           ++cnt;
         }
-        if (counter && ok)
-          __hip_atomic_fetch_add(&ecnt[id], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
       uint32_t place = 0, base = 0;
       uint64_t left = __ballot(ok);
@@ -644,12 +601,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))
       for (int cc = c; cc < kCols; cc += ngrp) s += red[gq * kCols + cc];
       if (s) atomicAdd(a.ws.rep_load + (static_cast<int64_t>(l) * G + (gq >> 5)) * even_up(P) + p, s);
     }
-  } else {
-    barrier_after_lds_atomics();
-  }
-  if (counter) {
-    for (int e = tid; e < E; e += nthreads)
-      if (ecnt[e]) atomicAdd(&a.ws.cnt[static_cast<int64_t>(l) * E + e], ecnt[e]);
   }
 }
 
