@@ -42,7 +42,7 @@ struct CountSegs {  // end token of every family
 };
 
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void ev_zero(EvArgs a) {
+__device__ __forceinline__ void zero_accumulators(const EvBase& a) {  // grid-stride
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
   const EvWs& w = a.ws;
@@ -66,6 +66,8 @@ __global__ __launch_bounds__(256) void ev_zero(EvArgs a) {
   }
 }
 
+__global__ __launch_bounds__(256) void ev_zero(EvBase a) { zero_accumulators(a); }
+
 // Trace validation and dispatch counts: every token-layer's ids, read once.  A workgroup takes a contiguous range of the
 // flattened trace (x = l * N + t) and walks the layers (with statistics: the families of the layers) it crosses,
 // counting the dispatches of every expert in LDS.  A token-layer with an id out of range or a repeated id is flagged,
@@ -74,7 +76,7 @@ __global__ __launch_bounds__(256) void ev_zero(EvArgs a) {
 // Bound by the read of the trace: the LDS adds of the counts hide behind it (2^19 tokens x 58 layers, top-8: 78 us
 // without them, and 100 us with them, while they cost the trace pass of few placements a fifth of its time).
 template <int K>
-__global__ __launch_bounds__(256) void ev_valid(EvArgs a, CountSegs segs) {
+__global__ __launch_bounds__(256) void ev_valid(EvBase a, CountSegs segs) {
   __shared__ uint32_t ecnt[TACG_MAX_EXPERTS];
   const int64_t total = a.N * a.L;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -147,71 +149,82 @@ __global__ __launch_bounds__(256) void ev_valid(EvArgs a, CountSegs segs) {
 // secondaries, 61 us with four).
 constexpr int kFlagsAhead = 4;
 
+// One expert's tables: error bits, and whether it has a (valid) secondary.
 template <int R>
-__global__ __launch_bounds__(256) void ev_flags(EvArgs a) {
+__device__ __forceinline__ bool has_secondary(uint8_t g0, const uint8_t* sec, int G, uint32_t& err) {
+  if (g0 >= G) err |= TACG_ERR_TABLE;
+  bool any = false;
+  uint32_t seen = g0 < G ? (1u << g0) : 0u;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint8_t g = sec[r];
+    if (g == kNone) continue;
+    if (g >= G || (seen >> g) & 1u) {
+      err |= TACG_ERR_TABLE;
+      continue;
+    }
+    seen |= 1u << g;
+    any = true;
+  }
+  return any;
+}
+
+template <int R>
+__global__ __launch_bounds__(256) void ev_flags(EvBase a) {
   const int64_t n = static_cast<int64_t>(a.P) * a.L * a.E;
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
   uint32_t err = 0;
   for (int64_t pe0 = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; pe0 < n; pe0 += kFlagsAhead * stride) {
-   uint8_t prim[kFlagsAhead], sec[kFlagsAhead][R > 0 ? R : 1];
+    uint8_t prim[kFlagsAhead], sec[kFlagsAhead][R > 0 ? R : 1];
 #pragma unroll
-   for (int u = 0; u < kFlagsAhead; ++u) {
-    const int64_t pe = min(pe0 + u * stride, n - 1);
-    prim[u] = a.primary[pe];
+    for (int u = 0; u < kFlagsAhead; ++u) {
+      const int64_t pe = min(pe0 + u * stride, n - 1);
+      prim[u] = a.primary[pe];
 #pragma unroll
-    for (int r = 0; r < R; ++r) sec[u][r] = a.secondary[pe * R + r];
-   }
+      for (int r = 0; r < R; ++r) sec[u][r] = a.secondary[pe * R + r];
+    }
 #pragma unroll
-   for (int u = 0; u < kFlagsAhead; ++u) {
-    const int64_t pe = pe0 + u * stride;
-    if (pe >= n) break;
-    const uint8_t g0 = prim[u];
-    if (g0 >= a.G) err |= TACG_ERR_TABLE;
-    bool any = false;
-    uint32_t seen = g0 < a.G ? (1u << g0) : 0u;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const uint8_t g = sec[u][r];
-      if (g == kNone) continue;
-      if (g >= a.G || (seen >> g) & 1u) {
-        err |= TACG_ERR_TABLE;
-        continue;
+    for (int u = 0; u < kFlagsAhead; ++u) {
+      const int64_t pe = pe0 + u * stride;
+      if (pe >= n) break;
+      if (has_secondary<R>(prim[u], sec[u], a.G, err)) {
+        // every placement marks the same few experts: set a bit only when a device-scope read does
+        // not show it yet (a stale read costs one extra atomic, never a missing bit)
+        const int e = static_cast<int>(pe % a.E);
+        const int l = static_cast<int>((pe / a.E) % a.L);
+        uint32_t* w = &a.ws.flagbits[l * 8 + (e >> 5)];
+        const uint32_t bit = 1u << (e & 31);
+        if (!(__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit)) atomicOr(w, bit);
       }
-      seen |= 1u << g;
-      any = true;
     }
-    if (any) {
-      // every placement marks the same few experts: set a bit only when a device-scope read does
-      // not show it yet (a stale read costs one extra atomic, never a missing bit)
-      const int e = static_cast<int>(pe % a.E);
-      const int l = static_cast<int>((pe / a.E) % a.L);
-      uint32_t* w = &a.ws.flagbits[l * 8 + (e >> 5)];
-      const uint32_t bit = 1u << (e & 31);
-      if (!(__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit)) atomicOr(w, bit);
-    }
-   }
   }
   if (err) atomicOr(a.d_err, err);
 }
 
-// Compact indices of the marked experts of each layer.  grid (L), 256 threads (one per expert).
-__global__ __launch_bounds__(256) void ev_replist(EvArgs a) {
-  __shared__ int32_t cnt;
-  const int l = blockIdx.x, e = threadIdx.x;
+// Compact indices of the marked experts of layer l (256 threads, one per expert), also into LDS.
+struct RepList {
+  int32_t cnt;
+  int32_t expert[TACG_MAX_REPLICATED];
+};
+
+__device__ __forceinline__ void list_replicated(const EvBase& a, int l, const uint32_t* bits, RepList& list) {
+  const int e = threadIdx.x;
+  int32_t& cnt = list.cnt;
   if (e == 0) cnt = 0;
   __syncthreads();
   if (e < a.E) {
-    const bool mark = (a.ws.flagbits[l * 8 + (e >> 5)] >> (e & 31)) & 1u;
+    const bool mark = (bits[e >> 5] >> (e & 31)) & 1u;
     // rank among marked experts = number of marked experts below e
     int rank = 0;
-    for (int q = 0; q < (e >> 5); ++q) rank += __popc(a.ws.flagbits[l * 8 + q]);
-    rank += __popc(a.ws.flagbits[l * 8 + (e >> 5)] & ((1u << (e & 31)) - 1u));
+    for (int q = 0; q < (e >> 5); ++q) rank += __popc(bits[q]);
+    rank += __popc(bits[e >> 5] & ((1u << (e & 31)) - 1u));
     uint8_t r = kNone;
     if (mark) {
       atomicAdd(&cnt, 1);
       if (rank < TACG_MAX_REPLICATED) {
         r = static_cast<uint8_t>(rank);
         a.ws.rep_list[l * TACG_MAX_REPLICATED + rank] = e;
+        list.expert[rank] = e;
       }
     }
     a.ws.rep_of[static_cast<int64_t>(l) * a.E + e] = r;
@@ -223,18 +236,23 @@ __global__ __launch_bounds__(256) void ev_replist(EvArgs a) {
   }
 }
 
+__global__ __launch_bounds__(256) void ev_replist(EvBase a) {  // grid (L)
+  __shared__ RepList list;
+  list_replicated(a, blockIdx.x, a.ws.flagbits + blockIdx.x * 8, list);
+}
+
 // Feasible candidates and fallback for every (placement, layer, replicated expert).  A wave takes four placements of a
 // layer, sixteen lanes each: the lanes first hold the placement's loads (two GPUs per lane) for the guard, then one replicated
 // expert each.  grid (ceil(P / 16), L), 256 threads.  Bound by latency: one thread per placement working through its sixteen
 // experts took 34 us for two placements and 44 us for 1024 (58 layers, 32 GPUs, 16 experts with three secondaries); this takes
 // 5 and 19 us.
-__global__ __launch_bounds__(256) void ev_repinfo(EvArgs a) {
+typedef int64_t RepLoads[16][TACG_MAX_GPUS];
+
+__device__ __forceinline__ void candidates_of(const EvBase& a, int l, int block, int nrep, const int32_t* experts,
+                                              RepLoads& loads) {
   static_assert(TACG_MAX_REPLICATED == 16 && TACG_MAX_GPUS == 32, "sixteen lanes per placement");
-  __shared__ int64_t loads[16][TACG_MAX_GPUS];
-  const int l = blockIdx.y, lane = threadIdx.x & 63, i16 = lane & 15, local = threadIdx.x >> 4;
-  const int p = blockIdx.x * 16 + local, pc = min(p, a.P - 1);
-  const int nrep = a.ws.n_rep[l];
-  if (nrep == 0) return;
+  const int lane = threadIdx.x & 63, i16 = lane & 15, local = threadIdx.x >> 4;
+  const int p = block * 16 + local, pc = min(p, a.P - 1);
   const int G = a.G;
   const int64_t* ref = a.load_ref + (static_cast<int64_t>(pc) * a.L + l) * G;
   int64_t v[2];
@@ -247,7 +265,7 @@ __global__ __launch_bounds__(256) void ev_repinfo(EvArgs a) {
   // this lane's expert: its candidate set
   uint32_t cand = 0;
   if (i16 < nrep) {
-    const int e = a.ws.rep_list[l * TACG_MAX_REPLICATED + i16];
+    const int e = experts[i16];
     const int64_t pe = (static_cast<int64_t>(pc) * a.L + l) * a.E + e;
     const uint8_t g0 = a.primary[pe];
     if (g0 < G) cand |= 1u << g0;
@@ -299,6 +317,44 @@ __global__ __launch_bounds__(256) void ev_repinfo(EvArgs a) {
   const uint32_t single = (__popc(cand) == 1) ? 0x80000000u : 0u;
   a.ws.rep_info[(static_cast<int64_t>(l) * TACG_MAX_REPLICATED + i16) * a.P + p] =
       make_uint2(fc, static_cast<uint32_t>(best) | single);
+}
+
+__global__ __launch_bounds__(256) void ev_repinfo(EvBase a) {
+  __shared__ RepLoads loads;
+  const int l = blockIdx.y, nrep = a.ws.n_rep[l];
+  if (nrep > 0) candidates_of(a, l, blockIdx.x, nrep, a.ws.rep_list + l * TACG_MAX_REPLICATED, loads);
+}
+
+// ev_zero, ev_flags, ev_replist and ev_repinfo in one launch, a workgroup per layer: all but the clearing is per layer.
+// For short tables only, where four launches cost more than the passes: at kPrepTables entries per layer a workgroup
+// takes about as long as they do.  grid (L), 256 threads.
+constexpr int64_t kPrepTables = 8192;
+
+template <int R>
+__global__ __launch_bounds__(256) void ev_prep(EvBase a) {
+  __shared__ uint32_t bits[8];
+  __shared__ RepList list;
+  __shared__ RepLoads loads;
+  const int l = blockIdx.x, tid = threadIdx.x;
+  zero_accumulators(a);
+  if (tid < 8) bits[tid] = 0;
+  __syncthreads();
+  uint32_t err = 0;
+  for (int i = tid; i < a.P * a.E; i += 256) {
+    const int p = i / a.E, e = i - p * a.E;
+    const int64_t pe = (static_cast<int64_t>(p) * a.L + l) * a.E + e;
+    uint8_t sec[R > 0 ? R : 1];
+#pragma unroll
+    for (int r = 0; r < R; ++r) sec[r] = a.secondary[pe * R + r];
+    if (has_secondary<R>(a.primary[pe], sec, a.G, err)) atomicOr(&bits[e >> 5], 1u << (e & 31));
+  }
+  barrier_after_lds_atomics();
+  list_replicated(a, l, bits, list);
+  __syncthreads();
+  const int nrep = min(list.cnt, TACG_MAX_REPLICATED);
+  if (R > 0 && nrep > 0)
+    for (int b = 0; b * 16 < a.P; ++b) candidates_of(a, l, b, nrep, list.expert, loads);
+  if (err) atomicOr(a.d_err, err);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -738,7 +794,7 @@ __global__ __launch_bounds__(kMainThreads) void ev_main(EvArgs a) {
 constexpr int kLoadWaves = 8;
 constexpr int kLoadRun = 64;  // placements per workgroup
 
-__global__ __launch_bounds__(64 * kLoadWaves) void ev_finalize(EvArgs a, uint64_t* __restrict__ cost_home,
+__global__ __launch_bounds__(64 * kLoadWaves) void ev_finalize(EvBase a, uint64_t* __restrict__ cost_home,
                                                                uint64_t* __restrict__ cost_span,
                                                                uint32_t* __restrict__ load,
                                                                uint64_t* __restrict__ cost_home_fam) {
@@ -844,7 +900,7 @@ int launch_main(const EvArgs& a, int n_pblocks, hipStream_t stream) {
 }
 
 template <int K>
-void launch_valid(const EvArgs& a, const CountSegs& segs, hipStream_t stream) {
+void launch_valid(const EvBase& a, const CountSegs& segs, hipStream_t stream) {
   // eight workgroups per CU; fewer when a workgroup would see less than 2048 token-layers (its counts are flushed once)
   const int blocks = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(2048, a.N * a.L / 2048)));
   hipLaunchKernelGGL(ev_valid<K>, dim3(blocks), dim3(256), 0, stream, a, segs);
@@ -1021,21 +1077,30 @@ int launch_eval(const int16_t* trace, int64_t N, int32_t L, int32_t K, int32_t E
   }
   a.n_pieces = np;
 
-  hipLaunchKernelGGL(ev_zero, dim3(256), dim3(256), 0, stream, a);
-  {
-    const int64_t n = static_cast<int64_t>(P) * L * E;
-    const int blocks = static_cast<int>(std::min<int64_t>(2048, (n + 256 * kFlagsAhead - 1) / (256 * kFlagsAhead)));
-const dim3 grid(blocks), block(256);
+  const EvBase& base = a;
+  const dim3 block(256);
+  if (static_cast<int64_t>(P) * E <= kPrepTables) {
     switch (R) {
-      case 0: hipLaunchKernelGGL(ev_flags<0>, grid, block, 0, stream, a); break;
-      case 1: hipLaunchKernelGGL(ev_flags<1>, grid, block, 0, stream, a); break;
-      case 2: hipLaunchKernelGGL(ev_flags<2>, grid, block, 0, stream, a); break;
-      case 3: hipLaunchKernelGGL(ev_flags<3>, grid, block, 0, stream, a); break;
-      default: hipLaunchKernelGGL(ev_flags<4>, grid, block, 0, stream, a); break;
+      case 0: hipLaunchKernelGGL(ev_prep<0>, dim3(L), block, 0, stream, base); break;
+      case 1: hipLaunchKernelGGL(ev_prep<1>, dim3(L), block, 0, stream, base); break;
+      case 2: hipLaunchKernelGGL(ev_prep<2>, dim3(L), block, 0, stream, base); break;
+      case 3: hipLaunchKernelGGL(ev_prep<3>, dim3(L), block, 0, stream, base); break;
+      default: hipLaunchKernelGGL(ev_prep<4>, dim3(L), block, 0, stream, base); break;
     }
+  } else {
+    hipLaunchKernelGGL(ev_zero, dim3(256), block, 0, stream, base);
+    const int64_t n = static_cast<int64_t>(P) * L * E;
+    const dim3 grid(static_cast<int>(std::min<int64_t>(2048, (n + 256 * kFlagsAhead - 1) / (256 * kFlagsAhead))));
+    switch (R) {
+      case 0: hipLaunchKernelGGL(ev_flags<0>, grid, block, 0, stream, base); break;
+      case 1: hipLaunchKernelGGL(ev_flags<1>, grid, block, 0, stream, base); break;
+      case 2: hipLaunchKernelGGL(ev_flags<2>, grid, block, 0, stream, base); break;
+      case 3: hipLaunchKernelGGL(ev_flags<3>, grid, block, 0, stream, base); break;
+      default: hipLaunchKernelGGL(ev_flags<4>, grid, block, 0, stream, base); break;
+    }
+    hipLaunchKernelGGL(ev_replist, dim3(L), block, 0, stream, base);
+    if (R > 0) hipLaunchKernelGGL(ev_repinfo, dim3((P + 15) / 16, L), block, 0, stream, base);
   }
-  hipLaunchKernelGGL(ev_replist, dim3(L), dim3(256), 0, stream, a);
-  if (R > 0) hipLaunchKernelGGL(ev_repinfo, dim3((P + 15) / 16, L), dim3(256), 0, stream, a);
   if (hipGetLastError() != hipSuccess) return TACG_E_DEVICE;
   if (np > 0) {
     const bool planes = stats == nullptr && eval_uses_planes(K, E, G);

@@ -59,7 +59,8 @@ inline EvWs carve_ev(void* ws, int64_t N, int32_t L, int32_t E, int32_t G, int32
   return r;
 }
 
-struct EvArgs {
+// Arguments of the passes around the trace pass (small: they are copied at every launch) ...
+struct EvBase {
   const int16_t* trace;
   const uint8_t* primary;
   const uint8_t* secondary;
@@ -69,10 +70,14 @@ struct EvArgs {
   int64_t N;
   int32_t L, K, E, F, G, P, R;
   int32_t theta_num, theta_den;
-  int32_t n_pieces;
-  int32_t n_pblocks;  // placement blocks of 64 * PPL placements
   int32_t stats;      // App. C statistics requested
   uint32_t band_starts;  // bit b: a family band starts at GPU b (the bands tile 0..G-1)
+};
+
+// ... and of ev_main and ev_stats.
+struct EvArgs : EvBase {
+  int32_t n_pieces;
+  int32_t n_pblocks;  // placement blocks of 64 * PPL placements
   // home band of family f: component f % 4 of band4[f / 4] = home_start | home_size << 8
   uint4 band4[TACG_MAX_FAMILIES / 4];
   // One record per piece of one family's tokens: (first token, end token, family offset,
@@ -121,12 +126,12 @@ struct TraceIds {
 
 // The bit-plane trace pass (eval_planes.hip): whether it takes these sizes, and its launch.
 bool eval_uses_planes(int32_t top_k, int32_t n_experts, int32_t n_gpus);
-int launch_eval_planes(const EvArgs& e, const int64_t* fam_off_host, const int32_t* home_start_host,
+int launch_eval_planes(const EvBase& e, const int64_t* fam_off_host, const int32_t* home_start_host,
                        const int32_t* home_size_host, hipStream_t stream);
 
 // The lane = token trace pass (eval_tokens.hip) for at most kFewPlacements placements, also with the App. C statistics.
 constexpr int32_t kFewPlacements = 24;
-int launch_eval_tokens(const EvArgs& e, const int64_t* fam_off_host, const int32_t* home_start_host,
+int launch_eval_tokens(const EvBase& e, const int64_t* fam_off_host, const int32_t* home_start_host,
                        const int32_t* home_size_host, hipStream_t stream);
 
 }  // namespace tacg

@@ -661,7 +661,7 @@ bool eval_uses_planes(int32_t K, int32_t E, int32_t G) {
   }
 }
 
-int launch_eval_planes(const EvArgs& e, const int64_t* fam_off_host, const int32_t* home_start_host,
+int launch_eval_planes(const EvBase& e, const int64_t* fam_off_host, const int32_t* home_start_host,
                        const int32_t* home_size_host, hipStream_t stream) {
   PlArgs a{};
   a.trace = e.trace;

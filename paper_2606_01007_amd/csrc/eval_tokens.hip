@@ -223,7 +223,7 @@ int launch_t(const TkArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-int launch_eval_tokens(const EvArgs& e, const int64_t* fam_off_host, const int32_t* home_start_host,
+int launch_eval_tokens(const EvBase& e, const int64_t* fam_off_host, const int32_t* home_start_host,
                        const int32_t* home_size_host, hipStream_t stream) {
   TkArgs a{};
   a.trace = e.trace;
