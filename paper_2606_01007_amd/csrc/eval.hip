@@ -888,8 +888,7 @@ int launch_main(const EvArgs& a, int n_pblocks, hipStream_t stream) {
   const size_t lds = static_cast<size_t>(a.E) * PW * 4 + static_cast<size_t>(2) * TACG_MAX_REPLICATED * PW * 4 +
                      static_cast<size_t>(a.G) * PW * 2 + align256(a.E) +
                      static_cast<size_t>(kRed * PW + 1) * 4;
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&ev_main<K, PPL, STATS>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+  allow_lds(&ev_main<K, PPL, STATS>, lds);
   EvArgs b = a;
   b.n_pblocks = n_pblocks;
   const int64_t grid = static_cast<int64_t>(n_pblocks) * a.n_pieces * a.L;

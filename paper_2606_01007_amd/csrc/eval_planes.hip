@@ -609,8 +609,7 @@ int launch_t(const PlArgs& a, hipStream_t stream) {
   const int threads = PlLayout<K, NP>::threads(a.E);
   const size_t lds = PlLayout<K, NP>::bytes(a.E, threads);
   if (lds > kLdsMax) return TACG_E_UNSUPPORTED;
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&ev_planes<K, NP>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+  allow_lds(&ev_planes<K, NP>, lds);
   const int64_t grid = static_cast<int64_t>(a.n_pblocks) * a.n_shares * a.L;
   if (grid > 0x7fffffff) return TACG_E_UNSUPPORTED;
   hipLaunchKernelGGL((ev_planes<K, NP>), dim3(static_cast<uint32_t>(grid)), dim3(threads), lds, stream, a);

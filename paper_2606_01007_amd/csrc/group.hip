@@ -163,8 +163,7 @@ void launch_sets(const float* a_tilde, int L, int E, const uint8_t* primary, int
   const dim3 grid((P + 64 * kSets - 1) / (64 * kSets), L);
   const bool words = E % 4 == 0 && reinterpret_cast<uintptr_t>(primary) % 4 == 0;
   auto* kernel = words ? &group_objective_kernel<true, kSets> : &group_objective_kernel<false, kSets>;
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            static_cast<int>(lds));
+  allow_lds(kernel, lds);
   hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds, stream, a_tilde, L, E, primary, P, G, obj, d_err);
 }
 

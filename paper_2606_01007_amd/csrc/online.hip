@@ -495,8 +495,7 @@ __global__ __launch_bounds__(kLanes) void on_main(OnArgs a) {
 template <int K, int NG, int MC>
 void launch_on_t(const OnArgs& a, hipStream_t stream) {
   const size_t lds = OnLayout<NG, MC>::kBytes;
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&on_main<K, NG, MC>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+  allow_lds(&on_main<K, NG, MC>, lds);
   hipLaunchKernelGGL((on_main<K, NG, MC>), dim3((a.P + kLanes - 1) / kLanes, a.L), dim3(kLanes), lds, stream, a);
 }
 

@@ -459,10 +459,8 @@ int launch_reweight(const uint32_t* D, const uint32_t* C, int32_t F, int32_t L, 
   const int rb = (E + kRows - 1) / kRows;
   const size_t plds = static_cast<size_t>(F) * E * sizeof(double);  // <= 64 x 256 x 8 = 128 KB
   const size_t slds = plds + 8 * static_cast<size_t>(E) * sizeof(double);
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&rw_pref), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            static_cast<int>(slds));
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&rw_graph), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            static_cast<int>(plds));
+  allow_lds(&rw_pref, slds);
+  allow_lds(&rw_graph, plds);
   const int nw = (F + kSums - 1) / kSums, rows = rows_per_block(L, E, nw), blocks = (E + rows - 1) / rows;
   hipLaunchKernelGGL(rw_rows, dim3(L, blocks), dim3(64 * nw), 2 * static_cast<size_t>(nw) * E * sizeof(double), stream, D,
                      C, F, L, E, k, rows, ws);

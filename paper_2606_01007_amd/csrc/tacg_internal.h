@@ -12,6 +12,14 @@ namespace tacg {
 // Round a byte count up to the 256-byte alignment used for every workspace sub-buffer.
 inline size_t align256(size_t x) { return (x + 255u) & ~size_t(255); }
 
+// Dynamic LDS of a launch: the runtime allows 64 KB by itself, so only more costs the call (about 1 us).
+template <class Kernel>
+inline void allow_lds(Kernel* kernel, size_t bytes) {
+  if (bytes > 65536)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              static_cast<int>(bytes));
+}
+
 // Workgroup barrier after LDS counters were incremented with relaxed atomics by several waves: first
 // wait until this wave's LDS operations have completed (s_waitcnt lgkmcnt(0)), then synchronise.
 // The compiler does not always emit that wait before the barrier after relaxed LDS atomics; without
