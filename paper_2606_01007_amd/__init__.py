@@ -48,6 +48,8 @@ class TacgError(RuntimeError):
 def lib():
     """The loaded libtacg.so (raises if it has not been built)."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
@@ -93,22 +95,22 @@ def _check(fn: str, status: int):
         raise TacgError(fn, status)
 
 
-def _dptr(t: Optional[torch.Tensor]):
+def _dptr(t: Optional[torch.Tensor]) -> Optional[int]:
     if t is None:
         return None
     if not t.is_cuda:
         raise ValueError("expected a device tensor")
     if not t.is_contiguous():
         raise ValueError("expected a contiguous tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()  # the argument types turn it into a pointer
 
 
-def _arg(t: Optional[torch.Tensor], name: str, dtype: torch.dtype, shape) -> Optional[ctypes.c_void_p]:
+def _arg(t: Optional[torch.Tensor], name: str, dtype: torch.dtype, shape) -> Optional[int]:
     """Device pointer of `t` after checking the element type and shape the C ABI assumes (a kernel
     would otherwise read or write past a smaller buffer)."""
     if t is None:
         return None
-    if t.dtype != dtype or tuple(t.shape) != tuple(int(x) for x in shape):
+    if t.dtype != dtype or t.shape != shape:
         raise ValueError(f"{name}: expected {dtype} {tuple(int(x) for x in shape)}, got {t.dtype} {tuple(t.shape)}")
     return _dptr(t)
 
@@ -120,8 +122,8 @@ def _trace_dims(trace: torch.Tensor):
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    # the handle alone: a Stream object per call costs more than the rest of the argument list
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) if stream is None else stream.cuda_stream
 
 
 def _host_i64(x) -> np.ndarray:
@@ -133,7 +135,7 @@ def _host_i32(x) -> np.ndarray:
 
 
 def _hptr(a: np.ndarray):
-    return a.ctypes.data_as(ctypes.c_void_p)
+    return a.__array_interface__["data"][0]  # `a` outlives the call; a ctypes pointer object costs several times this
 
 
 def _fam_off(fam_off) -> np.ndarray:
