@@ -1103,7 +1103,7 @@ int launch_eval(const int16_t* trace, int64_t N, int32_t L, int32_t K, int32_t E
   if (hipGetLastError() != hipSuccess) return TACG_E_DEVICE;
   if (np > 0) {
     const bool planes = stats == nullptr && eval_uses_planes(K, E, G);
-    const bool tokens = P <= kFewPlacements;
+    const bool tokens = eval_uses_tokens(P, R, planes);
     CountSegs segs;
     for (int f = 0; f < TACG_MAX_FAMILIES; ++f)
       segs.end[f] = f < F ? static_cast<uint32_t>(fam_off_host[f + 1]) : 0xffffffffu;
@@ -1112,8 +1112,8 @@ int launch_eval(const int16_t* trace, int64_t N, int32_t L, int32_t K, int32_t E
 #define TACG_K(k) \
   case k:         \
     launch_valid<k>(a, segs, stream);  \
-    rc = planes   ? launch_eval_planes(a, fam_off_host, home_start_host, home_size_host, stream) \
-         : tokens ? launch_eval_tokens(a, fam_off_host, home_start_host, home_size_host, stream) \
+    rc = tokens   ? launch_eval_tokens(a, fam_off_host, home_start_host, home_size_host, stream) \
+         : planes ? launch_eval_planes(a, fam_off_host, home_start_host, home_size_host, stream) \
                   : launch_main_k<k>(a, stream); \
     break;
       TACG_K(1) TACG_K(2) TACG_K(3) TACG_K(4) TACG_K(5) TACG_K(6) TACG_K(7) TACG_K(8)

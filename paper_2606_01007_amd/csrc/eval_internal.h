@@ -129,8 +129,14 @@ bool eval_uses_planes(int32_t top_k, int32_t n_experts, int32_t n_gpus);
 int launch_eval_planes(const EvBase& e, const int64_t* fam_off_host, const int32_t* home_start_host,
                        const int32_t* home_size_host, hipStream_t stream);
 
-// The lane = token trace pass (eval_tokens.hip) for at most kFewPlacements placements, also with the App. C statistics.
-constexpr int32_t kFewPlacements = 24;
+// The lane = token trace pass (eval_tokens.hip), also with the App. C statistics, and the numbers of placements it is
+// taken for.  Its time grows with the placements, the other passes' hardly do.  Measured on MI355X per call (top-8, 2^17
+// tokens x 16 layers), lane = token against lane = placement: E = 256, 32 GPUs, 16 x 3 replicas 204 / 312 us at 24
+// placements, 242 / 312 at 32, 358 / 309 at 48; E = 128, 16 GPUs, no replicas 126 / 188 us at 48, 135 / 190 at 64; against
+// bit planes (E = 128, 8 GPUs, 8 x 2 replicas) 63 / 84 us at 4, 86 / 85 at 8, 137 / 89 at 16.
+inline bool eval_uses_tokens(int32_t n_place, int32_t n_sec, bool planes) {
+  return n_place <= (planes ? 6 : n_sec > 0 ? 40 : 64);
+}
 int launch_eval_tokens(const EvBase& e, const int64_t* fam_off_host, const int32_t* home_start_host,
                        const int32_t* home_size_host, hipStream_t stream);
 

@@ -1,5 +1,5 @@
-// Placement scoring for few placements: the trace pass with lane = token (tacg_eval_placements and
-// tacg_eval_trace_stats with at most kFewPlacements placements).
+// Placement scoring for few placements (eval_uses_tokens): the trace pass of tacg_eval_placements and
+// tacg_eval_trace_stats with lane = token.
 //
 // The lane = placement pass (eval.hip) scores 128 placements per wave whatever their number, and walks the
 // tokens one by one.  Here a wave takes 64 tokens at once, one per lane, and up to four placements together: LDS

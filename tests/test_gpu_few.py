@@ -27,8 +27,12 @@ def _gpu():
     (64, 16, [300, 301], 32, 3, 4, 16, 2, 0),
     (20, 16, [500], 17, 4, 4, 16, 0, 1),
     (256, 8, [9000, 8191, 1], 32, 5, 3, 16, 4, 1),
-    (100, 7, [777] * 6, 31, 24, 3, 16, 0, 0),
-    (100, 7, [777] * 6, 31, 25, 3, 16, 0, 0),
+    (100, 7, [777] * 6, 31, 40, 3, 16, 0, 0),
+    (100, 7, [777] * 6, 31, 41, 3, 16, 0, 0),
+    (70, 6, [500, 3], 12, 64, 0, 0, 1, 0),
+    (70, 6, [500, 3], 12, 65, 0, 0, 1, 0),
+    (70, 6, [500, 3], 8, 6, 2, 8, 1, 0),                     # at most 8 GPUs: few placements, then bit planes
+    (70, 6, [500, 3], 8, 7, 2, 8, 1, 0),
     (40, 1, [300, 0, 0, 300], 10, 7, 1, 3, 2, 0),
 ])
 def test_few_placements(E, k, counts, G, P, R, n_rep, bad, big):
