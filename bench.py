@@ -94,7 +94,8 @@ def parse():
 
 
 # kernels whose HBM bytes are reported: the device kernels each one is made of, and their sources
-TRAFFIC_KERNELS = {"ev_main": (("ev_main",), ("eval.hip",)),
+TRAFFIC_KERNELS = {"ev_main": (("ev_main",), ("eval.hip", "eval_internal.h")),
+                   "ev_planes": (("ev_planes",), ("eval_planes.hip", "eval_internal.h")),
                    "coact_build": (("coact_hist_kernel", "coact_reduce_kernel"), ("coact.hip",))}
 
 
@@ -265,6 +266,7 @@ def run_config(name: str, args, all_mode: bool = False) -> dict:
     # a lower bound for any scoring on GPU masks in 32-bit lanes.
     eval_tops = ptl * (2 * k + 6) / t_eval / 1e12
     eval_tops_strict = ptl * (k + 2) / t_eval / 1e12
+    scorer = "ev_planes" if G <= 8 else "ev_main"
     result = {
         "metric": METRIC,
         "value": coact_rate,
@@ -294,17 +296,18 @@ def run_config(name: str, args, all_mode: bool = False) -> dict:
                     "trace_equivalent_frac": P * trace_bytes_s / t_eval / 1e9 / HBM_PEAK_GBS},
         "reweight_ms": t_rw * 1e3,
         "jain_ms": t_jain * 1e3,
-        "roofline": {"kernel": "ev_main (tacg_eval_placements)", "bound": "alu",
+        "roofline": {"kernel": f"{scorer} (tacg_eval_placements)", "bound": "alu",
                      "achieved": eval_tops, "peak": VALU_PEAK_TOPS, "unit": "T int32 lane-ops/s",
                      "frac": eval_tops / VALU_PEAK_TOPS,
                      "achieved_k_plus_2": eval_tops_strict, "frac_k_plus_2": eval_tops_strict / VALU_PEAK_TOPS,
-                     "traffic": None if reduced else measured_traffic("ev_main", cfg.name),
+                     "traffic": None if reduced else measured_traffic(scorer, cfg.name),
                      "note": "achieved/frac: 2k + 6 int32 lane-ops per placement-token-layer (k table "
                              "lookups, k-1 ORs of one-hot GPU masks, two popcounts, replica resolution); "
-                             "the lookups run on the LDS, one read serving all placements of a lane, so "
-                             "at four placements per lane (E <= 64) frac can exceed 1; *_k_plus_2: only "
-                             "the ORs, the and-not with the anchor bit and the two popcounts, a lower "
-                             "bound for any mask-based scoring; peak = 256 CUs x 64 lanes x 2.4 GHz"},
+                             "the lookups run on the LDS, one read serving all placements of a lane; "
+                             "*_k_plus_2: only the ORs, the and-not with the anchor bit and the two "
+                             "popcounts, a lower bound for any scoring with a mask per placement; "
+                             "ev_planes (up to 8 GPUs) works on bit planes, one lane-op for 32 "
+                             "placements, so both fractions can exceed 1 there; peak = 256 CUs x 64 lanes x 2.4 GHz"},
         "roofline_coact": {"kernel": ("coact_mfma" if tacg.coact_uses_matrix_cores(E, k) else "coact_hist")
                                      + " + coact_reduce (tacg_coact_build)", "bound": "hbm",
                            "achieved": coact_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
