@@ -172,31 +172,41 @@ __device__ __forceinline__ void lds_add(uint32_t* p, uint32_t v) {
   __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+
 // Reads dl rows 2q and 2q + 1 of this lane and leaves zeros behind (one LDS exchange of two dwords
-// 256 bytes apart).  The results are valid after wait_lds().
-__device__ __forceinline__ void lds_take_pair(const uint32_t* row0_lane, int q, uint32_t& x0, uint32_t& x1) {
-  typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+// 256 bytes apart).  To the compiler the result is there at once: it is valid, and may be used, only after
+// wait_exchanges().
+__device__ __forceinline__ v2u lds_take_pair(const uint32_t* row0_lane, int q) {
   v2u r;
   const uint32_t addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(row0_lane));
   asm volatile("ds_wrxchg2st64_rtn_b32 %0, %1, %2, %2 offset0:%3 offset1:%4"
                : "=v"(r)
                : "v"(addr), "v"(0u), "i"(2 * q), "i"(2 * q + 1)
                : "memory");
-  x0 = r.x;
-  x1 = r.y;
+  return r;
 }
 
-__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+// Waits until the exchanges into d are done, with BEHIND LDS operations of this wave issued after the last of them (the LDS
+// returns a wave's results in order).  A wait alone does not hold back the arithmetic on d, which touches no memory (its
+// conversions were compiled above the wait); the empty statements make every use of d depend on a point behind the
+// wait.  They take the registers in pairs, as the exchanges wrote them: taken singly, they were copied before the wait.
+template <int BEHIND, int NP>
+__device__ __forceinline__ void wait_exchanges(v2u (&d)[NP]) {
+  asm volatile("s_waitcnt lgkmcnt(%0)" ::"i"(BEHIND < 15 ? BEHIND : 15) : "memory");
+#pragma unroll
+  for (int q = 0; q < NP; q += 2) asm volatile("" : "+v"(d[q]), "+v"(d[q + 1]));
+}
 
 // eq. load-update: L_m <- fma(rho, L_m, d_m) (one rounding) for every GPU, and S = the new loads summed
 // in increasing GPU order (0 + L_0 = L_0).  Four GPUs per fixed instruction sequence, each add of S
 // placed between independent multiply-adds so that neither chain waits on the other's latency.
 template <int NG>
-__device__ __forceinline__ void update_loads(double (&Lm)[NG], const uint32_t (&dq)[NG], double rho, double& S) {
+__device__ __forceinline__ void update_loads(double (&Lm)[NG], const v2u (&dq)[NG / 2], double rho, double& S) {
 #pragma unroll
   for (int g = 0; g < NG; g += 4) {
-    const double d0 = static_cast<double>(dq[g]), d1 = static_cast<double>(dq[g + 1]);
-    const double d2 = static_cast<double>(dq[g + 2]), d3 = static_cast<double>(dq[g + 3]);
+    const double d0 = static_cast<double>(dq[g / 2].x), d1 = static_cast<double>(dq[g / 2].y);
+    const double d2 = static_cast<double>(dq[g / 2 + 1].x), d3 = static_cast<double>(dq[g / 2 + 1].y);
     asm volatile(
         "v_fma_f64 %0, %5, %0, %6\n"
         "v_fma_f64 %1, %5, %1, %7\n"
@@ -373,9 +383,9 @@ __global__ __launch_bounds__(kLanes) void on_main(OnArgs a) {
 
       // the previous served token's dispatch counts, cleared for this token (all zero before the
       // first served token, which then takes rho = 1: an exact no-op)
-      uint32_t dq[NG];
+      v2u dq[NG / 2];
 #pragma unroll
-      for (int q = 0; q < NG / 2; ++q) lds_take_pair(dl_lane, q, dq[2 * q], dq[2 * q + 1]);
+      for (int q = 0; q < NG / 2; ++q) dq[q] = lds_take_pair(dl_lane, q);
 
       // single-candidate slots: the set R of GPUs the token reaches, and their dispatches
       uint32_t c[K];
@@ -400,7 +410,7 @@ __global__ __launch_bounds__(kLanes) void on_main(OnArgs a) {
       const double rho_t = pending ? rho : 1.0;
       pending = true;
       double S = 0.0;
-      asm volatile("s_waitcnt lgkmcnt(%0)" ::"i"(K < 15 ? K : 15) : "memory");
+      wait_exchanges<K>(dq);
       update_loads<NG>(Lm, dq, rho_t, S);
       if (pend_any) {
 #pragma unroll
@@ -477,10 +487,10 @@ __global__ __launch_bounds__(kLanes) void on_main(OnArgs a) {
   }
   // the last served token's update
   if (pending) {
-    uint32_t dq[NG];
+    v2u dq[NG / 2];
 #pragma unroll
-    for (int q = 0; q < NG / 2; ++q) lds_take_pair(dl_lane, q, dq[2 * q], dq[2 * q + 1]);
-    wait_lds();
+    for (int q = 0; q < NG / 2; ++q) dq[q] = lds_take_pair(dl_lane, q);
+    wait_exchanges<0>(dq);
     double S = 0.0;
     update_loads<NG>(Lm, dq, rho, S);
   }
