@@ -520,7 +520,10 @@ __device__ __forceinline__ void score_piece(const EvArgs& a, const uint32_t* tbl
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nwaves = blockDim.x >> 6;
-  const int16_t* trace_l = a.trace + static_cast<int64_t>(l) * a.N * K;
+  // Tokens are counted from the piece's first, at most 2^26 of them, so that no step past its end wraps at the last
+  // tokens of a trace of nearly 2^32 (top-1).
+  const int16_t* trace_p = a.trace + (static_cast<int64_t>(l) * a.N + t_begin) * K;
+  const uint32_t n_piece = t_end - t_begin, pos0 = t_begin - off_f;  // pos0: the piece's position in its family
   S sc;
   sc.tbl_lane = reinterpret_cast<const char*>(tbl) + lane * PPL * 4;
   asm volatile("v_mov_b32 %0, %1" : "=v"(sc.row_bytes) : "i"(S::PW * 4));
@@ -533,8 +536,8 @@ __device__ __forceinline__ void score_piece(const EvArgs& a, const uint32_t* tbl
 #pragma unroll
   for (int q = 0; q < PPL; ++q) sc.acc_span[q] = sc.acc_home[q] = sc.acc_cross[q] = 0;
 
-  for (uint32_t r_begin = t_begin; r_begin < t_end; r_begin += round_tokens) {
-    const uint32_t r_end = min(t_end, r_begin + round_tokens);
+  for (uint32_t r_begin = 0; r_begin < n_piece; r_begin += round_tokens) {
+    const uint32_t r_end = min(n_piece, r_begin + round_tokens);
     for (uint32_t tile = r_begin + wave * 64u; tile < r_end; tile += nwaves * 64u) {
       // ---- per-lane preprocessing of token-layer (tile + lane) ----
       const uint32_t t = tile + lane;
@@ -545,14 +548,14 @@ __device__ __forceinline__ void score_piece(const EvArgs& a, const uint32_t* tbl
       // only the variant for traces with an invalid token-layer reads the marks)
       bool marked = false;
       if constexpr (CHECK) {
-        const int64_t x0 = static_cast<int64_t>(l) * a.N + tile;
+        const int64_t x0 = static_cast<int64_t>(l) * a.N + t_begin + tile;
         const int64_t g0 = x0 >> 6, g1 = min(x0 + 63, static_cast<int64_t>(L) * a.N - 1) >> 6;
         marked = (((a.ws.bad_tiles[g0 >> 5] >> (g0 & 31)) | (a.ws.bad_tiles[g1 >> 5] >> (g1 & 31))) & 1u) != 0u;
       }
       uint32_t info = 0;
       bool bad = false;
       if (t < r_end) {
-        const int16_t* idp = trace_l + static_cast<int64_t>(t) * K;
+        const int16_t* idp = trace_p + static_cast<int64_t>(t) * K;
         uint32_t raw[K];
 #pragma unroll
         for (int s = 0; s < K; ++s) raw[s] = static_cast<uint16_t>(idp[s]);
@@ -568,7 +571,7 @@ __device__ __forceinline__ void score_piece(const EvArgs& a, const uint32_t* tbl
           }
           pk[s >> 2] |= id << (8 * (s & 3));
         }
-        info |= ((t - off_f) % hz) << IL::kHomeShift;
+        info |= ((pos0 + t) % hz) << IL::kHomeShift;
         if (marked) {
           // an invalid token-layer (flagged by ev_valid) is not scored; its ids stay clamped in
           // range, unused

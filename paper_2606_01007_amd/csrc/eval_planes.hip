@@ -363,13 +363,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))
     const FamRec fr = a.fam[f];
     const uint32_t hs = fr.band & 0xffu, hz = fr.band >> 8;
     const uint32_t n_f = fr.end - fr.off;
-    const uint32_t per_class = ((n_f + hz - 1) / hz + 63) / 64;  // tiles of a class
+    const uint32_t per_class = (n_f - 1) / hz / 64 + 1;          // tiles of a class (the run has a tile: n_f > 0)
     const uint32_t pos = (x0 - fr.first_tile) / per_class;
     const uint32_t class0 = fr.first_tile + pos * per_class;
     const uint32_t xe = min(x1, class0 + per_class);
     const uint32_t h = hs + pos;
     const uint32_t c0 = (x0 - class0) * 64;                      // first token of the run, within the class
-    const uint32_t c1 = min(n_f > pos ? (n_f - pos + hz - 1) / hz : 0u, (xe - class0) * 64);
+    uint32_t c1 = n_f > pos ? (n_f - pos - 1) / hz + 1 : 0u;     // the class's tokens
+    if (xe - class0 < per_class) c1 = min(c1, (xe - class0) * 64);
     // the waves take the share's tiles in turn, across runs (so none exceeds its part of kMaxTiles)
     const uint32_t first = (wave + nwaves - (x0 - share0) % nwaves) % nwaves;
     x0 = xe;
@@ -385,20 +386,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3))
     cost[0].clear();
     cost[1].clear();
     uint32_t n_step = 0;  // pushes so far (wave-uniform)
-    const int16_t* trace_c = a.trace + (static_cast<int64_t>(l) * a.N + fr.off + pos) * K;
-    const uint32_t ntile = (c1 - c0 + 63) / 64;
+    const int16_t* trace_c = a.trace + (static_cast<int64_t>(l) * a.N + fr.off + pos + static_cast<int64_t>(c0) * hz) * K;
+    const uint32_t n_run = c1 - c0, ntile = (n_run + 63) / 64;   // at most kMaxTiles tiles
     TraceIds<K> next;  // the ids of the wave's next tile, in flight while the current one is scored
-    next.fetch(trace_c + static_cast<int64_t>(min(c0 + first * 64 + lane, c1 - 1)) * hz * K);
+    next.fetch(trace_c + static_cast<int64_t>(min(first * 64 + lane, n_run - 1)) * hz * K);
     __syncthreads();  // the tables are in place
     for (uint32_t tile = first; tile < ntile; tile += nwaves) {
     // ---- one token per lane: descriptor, sorted by the number of replicated slots ----
-    const uint32_t ci = c0 + tile * 64 + lane;
-    const bool in = ci < c1;
+    const uint32_t ci = tile * 64 + lane;  // within the run: a class may end just below 2^32
+    const bool in = ci < n_run;
     uint32_t nvalid;
     {
       uint32_t raw[K];
       next.unpack(raw);
-      next.fetch(trace_c + static_cast<int64_t>(min(ci + nwaves * 64, c1 - 1)) * hz * K);
+      next.fetch(trace_c + static_cast<int64_t>(min(ci + nwaves * 64, n_run - 1)) * hz * K);
       bool ok = in;
       if (any_bad) {  // some token-layer of the trace is invalid: leave those out
         bool dup = false;

@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kThreads) void ev_tokens(TkArgs a) {
   const TkFam fr = a.fam[f];
   const uint32_t hs = fr.band & 0xffu, hz = fr.band >> 8;
   const uint32_t t0 = fr.off + (piece - fr.first_piece) * a.chunk;
-  const uint32_t t1 = min(fr.end, t0 + a.chunk);
+  const uint32_t n = min(fr.end - t0, a.chunk);  // tokens are counted from t0: t0 + chunk may pass 2^32
 
   // ---- tables ----
   const int nrep = a.ws.n_rep[l];
@@ -95,16 +95,17 @@ __global__ __launch_bounds__(kThreads) void ev_tokens(TkArgs a) {
   __syncthreads();
 
   const bool any_bad = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(*a.ws.n_bad != 0u)) != 0u;
-  const int16_t* trace_l = a.trace + static_cast<int64_t>(l) * a.N * K;
+  const int16_t* trace_c = a.trace + (static_cast<int64_t>(l) * a.N + t0) * K;
+  const uint32_t pos0 = t0 - fr.off;
   uint32_t span[kPB] = {}, away[kPB] = {}, cross[kPB] = {}, scored = 0;
   TraceIds<K> next;  // the next tile's ids are in flight while one is scored
-  next.fetch(trace_l + static_cast<int64_t>(min(t0 + tid, t1 - 1)) * K);
-  for (uint32_t tile = t0 + wave * 64; tile < t1; tile += kThreads) {
+  next.fetch(trace_c + static_cast<int64_t>(min(static_cast<uint32_t>(tid), n - 1)) * K);
+  for (uint32_t tile = wave * 64; tile < n; tile += kThreads) {
     const uint32_t t = tile + lane;
     uint32_t id[K];
     next.unpack(id);
-    next.fetch(trace_l + static_cast<int64_t>(min(t + kThreads, t1 - 1)) * K);
-    bool ok = t < t1;
+    next.fetch(trace_c + static_cast<int64_t>(min(t + kThreads, n - 1)) * K);
+    bool ok = t < n;
     if (any_bad) {  // some token-layer of the trace is invalid: leave those out
       bool dup = false;
 #pragma unroll
@@ -116,7 +117,7 @@ __global__ __launch_bounds__(kThreads) void ev_tokens(TkArgs a) {
       ok &= !dup;
     }
     scored += ok ? 1u : 0u;
-    const uint32_t h = hs + (t - fr.off) % hz;
+    const uint32_t h = hs + (pos0 + t) % hz;
     uint32_t m[kPB] = {};
     uint64_t reps = 0;  // the replicated slots' indices in slot order, four bits each
     uint32_t cnt = 0;
