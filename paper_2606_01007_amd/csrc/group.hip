@@ -1,7 +1,8 @@
 // Grouping objective of Sec. 3.3 (eq. grouping-objective) for many placements: the within-group
 // affinity  obj[p][l] = sum_m sum_{e != e' on GPU m} A-tilde_l(e, e'),  accumulated in float64.
 //
-// Lane = placement; a workgroup takes SETS x 64 placements of one layer, SETS of them per lane.
+// group_objective_kernel (many placements): lane = placement; a workgroup takes SETS x 64 placements of one layer, SETS of
+// them per lane.
 //   1. One wave per 64 placements links the experts of every GPU into a ring, next[e][lane][set] in LDS: going
 //      down the expert ids, one LDS exchange of the GPU's head with the expert yields its successor; the
 //      last expert of a GPU is linked to its first at the end.  Heads and tails are lane-private dwords, and the
@@ -10,10 +11,13 @@
 //      lane walks its placement's ring of e's GPU, adding the row's entries: two LDS reads and one float64
 //      add per pair, all lanes busy when the GPUs hold equally many experts.
 //   3. The waves' sums are added in wave order.
+// What bounds it: the row entries' LDS reads (random banks) and VALU issue.  Measured on MI355X at E = 256, 32 GPUs, 1024
+// placements x 58 layers (1.1e8 entries), device time: 427 -> 67 us against one workgroup per (placement, layer).
 //
-// What bounds it: the row entries' LDS reads (random banks) and VALU issue.  Gathering the
-// entries from L2 instead, one lane per expert with lists by ballots, was bound by the cache lines per load.
-// Measured on MI355X at E = 256, 32 GPUs, 1024 placements x 58 layers (1.1e8 entries): 427 -> 67 us.
+// group_gather_kernel (few placements): one workgroup per (placement, layer) lists the experts of every GPU by ballots, then
+// thread e gathers the entries of its own A-tilde row at the other members of its GPU from L2.  Bound by the cache
+// lines per load once the chip is full; below that its chain is one GPU's members long, where a wave of the rings walks
+// E / 16 of them (the rings take about as long for one placement as for 64).
 #include "tacg_internal.h"
 
 namespace tacg {
@@ -156,6 +160,80 @@ __global__ __launch_bounds__(kThreads) void group_objective_kernel(const float* 
   if (err) atomicOr(d_err, err);
 }
 
+// Few placements.  grid (P, L), one thread per expert.
+constexpr int kGatherThreads = 256;
+
+__global__ __launch_bounds__(kGatherThreads) void group_gather_kernel(const float* __restrict__ a_tilde, int L, int E,
+                                                                      const uint8_t* __restrict__ primary, int G,
+                                                                      double* __restrict__ obj, uint32_t* d_err) {
+  constexpr int kGatherWaves = kGatherThreads / 64;
+  __shared__ unsigned long long lanes_of[kGatherWaves][TACG_MAX_GPUS];  // lanes of each wave holding GPU m
+  __shared__ int start[TACG_MAX_GPUS + 1];                              // list offsets per GPU
+  __shared__ uint8_t member[TACG_MAX_EXPERTS];                          // experts grouped by GPU, ids increasing
+  __shared__ double part[kGatherWaves];
+  const int p = blockIdx.x, l = blockIdx.y;
+  const int e = threadIdx.x;
+  const int lane = e & 63, wave = e >> 6;
+  uint32_t err = 0;
+  uint32_t g = 0xFF;  // 0xFF: no expert, or left out of every group (a table error)
+  if (e < E) {
+    g = primary[(static_cast<int64_t>(p) * L + l) * E + e];
+    if (g >= static_cast<uint32_t>(G)) {
+      err = TACG_ERR_TABLE;
+      g = 0xFF;
+    }
+  }
+  for (int m = 0; m < G; ++m) {
+    const unsigned long long b = __ballot(g == static_cast<uint32_t>(m));
+    if (lane == 0) lanes_of[wave][m] = b;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int s = 0;
+    for (int m = 0; m < G; ++m) {
+      start[m] = s;
+      for (int w = 0; w < kGatherWaves; ++w) s += __popcll(lanes_of[w][m]);
+    }
+    start[G] = s;
+  }
+  __syncthreads();
+  if (g != 0xFF) {
+    int rank = __popcll(lanes_of[wave][g] & ((1ull << lane) - 1ull));
+    for (int w = 0; w < wave; ++w) rank += __popcll(lanes_of[w][g]);
+    member[start[g] + rank] = static_cast<uint8_t>(e);
+  }
+  __syncthreads();
+  double acc = 0.0;
+  if (g != 0xFF) {
+    const float* row = a_tilde + (static_cast<int64_t>(l) * E + e) * E;
+    const int b0 = start[g], b1 = start[g + 1];
+#pragma unroll 4
+    for (int i = b0; i < b1; ++i) {
+      const int e2 = member[i];
+      if (e2 != e) acc += static_cast<double>(row[e2]);
+    }
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o, 64);
+  if (lane == 0) part[wave] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double s = 0.0;
+    for (int w = 0; w < kGatherWaves; ++w) s += part[w];
+    obj[static_cast<int64_t>(p) * L + l] = s;
+  }
+  if (err) atomicOr(d_err, err);
+}
+
+// Where the gather takes over: placements x layers, by the experts per GPU (its time grows with all three, the rings' only
+// with the last until their workgroups fill the chip).  Device times on MI355X, gather / rings in us: 256 experts on 2
+// GPUs 128 / 187 at 1024 rows, 194 / 186 at 1508, 253 / 186 at 2048; on 8 GPUs 70 / 78 at 2048, 115 / 77 at 3016; on 32 GPUs
+// 46 / 48 at 3016, 68 / 48 at 6032; 64 experts on 8 GPUs 12.2 / 13.6 at 3016, 18.7 / 14.1 at 6032; 16 experts on 8 GPUs 5.7
+// / 5.1 at 2048, 7.9 / 5.2 at 3016.  One placement of 2 layers: 256 experts on 2, 8 and 32 GPUs 25 / 180, 11 / 74 and 9 / 44.
+bool group_uses_gather(int64_t rows, int E, int G) {
+  return rows <= (E >= 64 && E <= 8 * G ? 3072 : E <= 32 * G ? 2048 : 1536);
+}
+
 template <int kSets>
 void launch_sets(const float* a_tilde, int L, int E, const uint8_t* primary, int P, int G, double* obj, uint32_t* d_err,
                  hipStream_t stream) {
@@ -171,6 +249,10 @@ void launch_sets(const float* a_tilde, int L, int E, const uint8_t* primary, int
 
 int launch_group_objective(const float* a_tilde, int32_t L, int32_t E, const uint8_t* primary, int32_t P, int32_t G,
                            double* obj, uint32_t* d_err, hipStream_t stream) {
+  if (group_uses_gather(static_cast<int64_t>(P) * L, E, G)) {
+    hipLaunchKernelGGL(group_gather_kernel, dim3(P, L), dim3(kGatherThreads), 0, stream, a_tilde, L, E, primary, G, obj, d_err);
+    return hipGetLastError() == hipSuccess ? TACG_OK : TACG_E_DEVICE;
+  }
   // as many placements per workgroup as still leave the chip about one workgroup per CU (a workgroup's rows of A-tilde
   // serve all its placements)
   const int64_t sets = (P + 63) / 64;
