@@ -20,6 +20,8 @@
 //   * At E <= 64 with k >= 4, and at E <= 128 with 8 <= k <= 12, the partial slots come from 4-bit
 //     matrix products instead (coact_mfma.hip), with the same split of x, the same slots and the
 //     same reduction.
+#include <cmath>
+
 #include "tacg_internal.h"
 
 namespace tacg {
@@ -407,8 +409,17 @@ size_t coact_bins(int32_t n_experts, int32_t top_k) {
   return static_cast<size_t>(n_experts) * static_cast<size_t>(n_experts - 1) / 2;
 }
 
-int coact_num_workgroups(int64_t total, int32_t n_experts, int32_t top_k) {
-  if (coact_uses_mfma(n_experts, top_k)) return coact_mfma_workgroups(total, n_experts);
+// Counting takes total x a / W, and the reduction of a segment W / segments + 1 slots of b each, one after the other: their
+// sum is least at W = sqrt(total x segments x a / b).  Measured on MI355X: a = 0.3 + 0.03 k (k - 1) ns per token-layer
+// (matrix path: 3.5 ns at E <= 64, 8 ns above), b = 0.15, 0.32, 0.72 and 1.28 us per slot at up to 64, 128, 192 and 256
+// experts.  Without this limit, one segment took, per call: E = 256, top-2, 374006 tokens 374 us with 256 workgroups against 40
+// with 8; E = 160, top-6, 200000 tokens 234 against 40 with 16; E = 64, top-8, 2 layers x 500000 tokens 112 against 55 with 128.
+int coact_num_workgroups(int64_t total, double segments, int32_t n_experts, int32_t top_k) {
+  const int nq = (n_experts + 63) / 64;
+  const double a = coact_uses_mfma(n_experts, top_k) ? (nq == 1 ? 3.5 : 8.0) : 0.3 + 0.03 * top_k * (top_k - 1);
+  const double b = nq == 1 ? 150.0 : 80.0 * nq * nq;
+  const double best = std::sqrt(static_cast<double>(total) * segments * a / b);
+  if (coact_uses_mfma(n_experts, top_k)) return coact_mfma_workgroups(total, best, n_experts);
   // E > 128: the triangle needs more than half of the 160 KB LDS, so one 1024-thread workgroup per
   // CU; otherwise four 512-thread workgroups per CU (the same 32 waves, with four private triangles)
   const int64_t cap = (n_experts > kCoactSmallE) ? 256 : 1024;
@@ -417,7 +428,8 @@ int coact_num_workgroups(int64_t total, int32_t n_experts, int32_t top_k) {
   // 16384 265 -> 118 us (both 16 families: the dense counts written are 243 MB), x 65536 169 -> 140 us; E = 100, top-6, 12 layers
   // x 30000 tokens 60.5 -> 18.6 us (22.1 at 1024 per workgroup).
   const int64_t per = (n_experts > kCoactSmallE) ? 1024 : 2048;
-  const int64_t want = (total + per - 1) / per;
+  const int64_t most = (total + per - 1) / per, least = (total + 32767) / 32768;
+  const int64_t want = std::max(least, static_cast<int64_t>(std::min(static_cast<double>(most), best)));
   return static_cast<int>(std::max<int64_t>(1, std::min(cap, want)));
 }
 
@@ -432,7 +444,10 @@ int launch_coact(const int16_t* trace, int64_t n_tokens, int32_t n_layers, int32
   a.K = top_k;
   a.E = n_experts;
   a.F = n_fam;
-  a.W = coact_num_workgroups(a.total, n_experts, top_k);
+  // the longest segment's slots are the reduction's chain: as many segments of that length as the trace holds
+  int64_t longest = 1;
+  for (int f = 0; f < n_fam; ++f) longest = std::max(longest, fam_off_host[f + 1] - fam_off_host[f]);
+  a.W = coact_num_workgroups(a.total, static_cast<double>(a.total) / longest, n_experts, top_k);
   a.nbins = static_cast<int32_t>(coact_bins(n_experts, top_k));
   a.partial = static_cast<uint32_t*>(workspace);
   a.d_err = d_err;

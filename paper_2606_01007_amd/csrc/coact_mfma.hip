@@ -371,15 +371,16 @@ bool coact_uses_mfma(int32_t n_experts, int32_t top_k) {
   return (n_experts <= 64 && top_k >= 4) || (n_experts <= 128 && top_k >= 8 && top_k <= 12);
 }
 
-int coact_mfma_workgroups(int64_t total, int32_t n_experts) {
+int coact_mfma_workgroups(int64_t total, double best, int32_t n_experts) {
   // One wave per workgroup.  Short traces are bound by the length of a wave's chain of batches, so they are split
   // down to 1024 token-layers a wave; from 1536 waves on the partial slots cost more than the shorter chains save until a
-  // wave holds 8192 token-layers; at most 16 waves per CU at E <= 64 and 8 at E <= 128 (all resident).  Measured per call on
+  // wave holds 8192 token-layers; no more than `best` (coact_num_workgroups) below that; at most 16 waves per CU at E <= 64 and 8 at E <= 128 (all resident).  Measured per call on
   // MI355X against one wave per 8192 token-layers: E = 60, top-4, 6 x 20000 tokens x 24 layers 46.0 -> 32.2 us, 20000 tokens
   // x 24 layers 51.0 -> 21.8 us; E = 64, top-6, 2^18 tokens x 27 layers 44.2 -> 38.4 us; E = 128, top-8, 2^14 tokens x 48
   // layers 155.9 -> 43.9 us (60.5 with 2048 a wave), 2^16 tokens 105.0 -> 62.0 us (81.7 with 1024 a wave).
   const int64_t cap = n_experts <= 64 ? 4096 : 2048;
-  const int64_t want = std::max<int64_t>(std::min<int64_t>((total + 1023) / 1024, 1536), (total + 8191) / 8192);
+  const int64_t most = std::min<int64_t>((total + 1023) / 1024, 1536), least = (total + 8191) / 8192;
+  const int64_t want = std::max(least, static_cast<int64_t>(std::min(static_cast<double>(most), best)));
   return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(cap, want)));
 }
 
