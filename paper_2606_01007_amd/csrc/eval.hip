@@ -26,6 +26,8 @@
 //     indices; the per-token loop broadcasts them with v_readlane, so the ids live in SGPRs.
 //   * Per token-layer and lane: k conflict-free LDS reads (64 consecutive dwords per wave), OR of the
 //     masks, then (rarely) the replicated slots, then two popcounts into per-lane accumulators.
+#include <algorithm>
+
 #include "eval_internal.h"
 
 namespace tacg {
@@ -86,14 +88,20 @@ __global__ __launch_bounds__(256) void ev_valid(EvBase a, CountSegs segs) {
   uint32_t err = 0;
   for (int e = tid; e < a.E; e += blockDim.x) ecnt[e] = 0;
   __syncthreads();
+  // the families' ends, one per lane: a segment's family is the number of ends at or before its first token
+  static_assert(TACG_MAX_FAMILIES == 64, "a family per lane");
+  const uint32_t fam_end = a.stats ? segs.end[lane] : 0u;
+  int64_t l = pos / a.N, layer0 = l * a.N;  // layer of pos, and its first token-layer
   while (pos < end) {
-    const int64_t l = pos / a.N;
+    if (pos - layer0 >= a.N) {
+      ++l;
+      layer0 += a.N;
+    }
     int f = 0;
-    int64_t stop = min(end, (l + 1) * a.N);
+    int64_t stop = min(end, layer0 + a.N);
     if (a.stats) {
-      const int64_t t = pos - l * a.N;
-      while (static_cast<int64_t>(segs.end[f]) <= t) ++f;
-      stop = min(end, l * a.N + static_cast<int64_t>(segs.end[f]));
+      f = __popcll(__ballot(static_cast<int64_t>(fam_end) <= pos - layer0));
+      stop = min(end, layer0 + static_cast<uint32_t>(__builtin_amdgcn_readlane(fam_end, f)));
     }
     const int64_t last = stop - 1;
     constexpr int kAhead = 2;  // steps in flight behind the current one
@@ -103,6 +111,7 @@ __global__ __launch_bounds__(256) void ev_valid(EvBase a, CountSegs segs) {
     for (int64_t xb = pos; xb < stop; xb += kAhead * 256) {
 #pragma unroll
       for (int d = 0; d < kAhead; ++d) {
+        if (d > 0 && xb + d * 256 >= stop) break;  // a short segment: no step for its end
         const int64_t x = xb + d * 256 + tid;
         uint32_t raw[K];
         ring[d].unpack(raw);
@@ -903,8 +912,14 @@ int launch_main(const EvArgs& a, int n_pblocks, hipStream_t stream) {
 
 template <int K>
 void launch_valid(const EvBase& a, const CountSegs& segs, hipStream_t stream) {
-  // eight workgroups per CU; fewer when a workgroup would see less than 2048 token-layers (its counts are flushed once)
-  const int blocks = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(2048, a.N * a.L / 2048)));
+  // Eight workgroups per CU; fewer when a workgroup would see less than 2048 token-layers (its counts are flushed once).  A
+  // short trace is bound by a workgroup's chain: segments (layers, with statistics their families), 2 to 5 us each, and steps.  So
+  // at least two workgroups per segment, and one per step up to 256.  Whole statistics calls, one workgroup per 2048
+  // token-layers against this: 64 families, 561 tokens x 4 layers, 64 placements 534 -> 49 us; 1939 tokens, 65 placements 353 -> 56 us;
+  // 2^19 tokens x 4 layers of 8 experts are slower split further (46 against 54 us: more adds to few counters).
+  const int64_t total = a.N * a.L, segments = static_cast<int64_t>(a.L) * (a.stats ? a.F : 1);
+  const int64_t want = std::max({total / 2048, 2 * segments, std::min<int64_t>(total / 256, 256)});
+  const int blocks = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(2048, want)));
   hipLaunchKernelGGL(ev_valid<K>, dim3(blocks), dim3(256), 0, stream, a, segs);
 }
 
