@@ -801,17 +801,16 @@ __global__ __launch_bounds__(kMainThreads) void ev_main(EvArgs a) {
   }
 }
 
-// Loads and costs.  A workgroup takes one layer and kLoadRun placements, a wave one placement at a time, as
-// placement_load_kernel.  grid (ceil(P / kLoadRun), L).
+// Loads and costs.  A workgroup takes one layer and `run` placements, a wave one placement at a time, as
+// placement_load_kernel.  grid (ceil(P / run), L).
 constexpr int kLoadWaves = 8;
-constexpr int kLoadRun = 64;  // placements per workgroup
 
-__global__ __launch_bounds__(64 * kLoadWaves) void ev_finalize(EvBase a, uint64_t* __restrict__ cost_home,
+__global__ __launch_bounds__(64 * kLoadWaves) void ev_finalize(EvBase a, int run, uint64_t* __restrict__ cost_home,
                                                                uint64_t* __restrict__ cost_span,
                                                                uint32_t* __restrict__ load,
                                                                uint64_t* __restrict__ cost_home_fam) {
   __shared__ uint32_t acc[kLoadWaves][TACG_MAX_GPUS];
-  const int l = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const int E = a.E, G = a.G, L = a.L;
   // dispatches of the experts that are served by their primary in every placement (a replicated one's are its choices)
   uint32_t d[4];
@@ -821,7 +820,7 @@ __global__ __launch_bounds__(64 * kLoadWaves) void ev_finalize(EvBase a, uint64_
     const int64_t le = static_cast<int64_t>(l) * E + min(e, E - 1);
     d[q] = e < E && a.ws.rep_of[le] == kNone ? a.ws.cnt[le] : 0u;
   }
-  const int p1 = min(a.P, static_cast<int>(blockIdx.x + 1) * kLoadRun);
+  const int p1 = min(a.P, static_cast<int>(blockIdx.x + 1) * run);
   uint8_t next[4];
   uint32_t next_rep = 0;
   auto fetch = [&](int p) {
@@ -831,14 +830,14 @@ __global__ __launch_bounds__(64 * kLoadWaves) void ev_finalize(EvBase a, uint64_
     for (int q = 0; q < 4; ++q) next[q] = src[min(lane + 64 * q, E - 1)];
     next_rep = a.ws.rep_load[(static_cast<int64_t>(l) * G + min(lane, G - 1)) * even_up(a.P) + pc];
   };
-  int p = blockIdx.x * kLoadRun + wave;
+  int p = blockIdx.x * run + wave;
   fetch(p);
-  for (; p < p1; p += kLoadWaves) {
+  for (; p < p1; p += nw) {
     uint32_t g[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) g[q] = next[q];
     const uint32_t rep = next_rep;
-    fetch(p + kLoadWaves);
+    fetch(p + nw);
     if (lane < G) acc[wave][lane] = rep;
     __asm__ __volatile__("" ::: "memory");  // the LDS keeps a wave's operations in order
 #pragma unroll
@@ -939,11 +938,12 @@ int launch_main_k(const EvArgs& a, hipStream_t stream) {
 // summed the families again each time).
 __global__ __launch_bounds__(64 * kLoadWaves) void placement_load_kernel(const uint32_t* __restrict__ D, int F, int L,
                                                                          int E, const uint8_t* __restrict__ primary,
-                                                                         int P, int G, int64_t* __restrict__ load_ref,
+                                                                         int P, int G, int run,
+                                                                         int64_t* __restrict__ load_ref,
                                                                          uint32_t* d_err) {
   __shared__ unsigned long long acc[kLoadWaves][TACG_MAX_GPUS];
   __shared__ unsigned long long sum[TACG_MAX_EXPERTS];
-  const int l = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   for (int e = threadIdx.x; e < E; e += blockDim.x) {
     unsigned long long s = 0;
 #pragma unroll 8
@@ -954,7 +954,7 @@ __global__ __launch_bounds__(64 * kLoadWaves) void placement_load_kernel(const u
   unsigned long long d[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) d[q] = lane + 64 * q < E ? sum[lane + 64 * q] : 0ull;
-  const int p1 = min(P, static_cast<int>(blockIdx.x + 1) * kLoadRun);
+  const int p1 = min(P, static_cast<int>(blockIdx.x + 1) * run);
   uint32_t err = 0;
   uint8_t next[4];
   auto fetch = [&](int p) {
@@ -962,13 +962,13 @@ __global__ __launch_bounds__(64 * kLoadWaves) void placement_load_kernel(const u
 #pragma unroll
     for (int q = 0; q < 4; ++q) next[q] = src[min(lane + 64 * q, E - 1)];
   };
-  int p = blockIdx.x * kLoadRun + wave;
+  int p = blockIdx.x * run + wave;
   fetch(p);
-  for (; p < p1; p += kLoadWaves) {
+  for (; p < p1; p += nw) {
     uint32_t g[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) g[q] = next[q];
-    fetch(p + kLoadWaves);
+    fetch(p + nw);
     if (lane < G) acc[wave][lane] = 0;
     __asm__ __volatile__("" ::: "memory");  // the LDS keeps a wave's operations in order
 #pragma unroll
@@ -1026,6 +1026,21 @@ __global__ __launch_bounds__(64) void jain_kernel(const uint32_t* __restrict__ l
 }
 
 }  // namespace
+
+// Placements per workgroup of the load passes: 64 share a layer's sums, but few placements are bound by a wave's chain of them,
+// so they are spread until the chip holds about 512 workgroups.  placement_load at 8, 16, 32 and 64 per workgroup, device time in
+// us: 90 placements x 12 layers, E = 252, 3.4, 4.2, 5.3 and 7.8; 400 x 12, E = 256, 16 families, 5.1, 5.4, 5.8 and 7.6; 256 x 58
+// 8.9, 7.0, 7.0 and 7.8; 512 x 24, E = 60, 5.5, 4.3, 4.6 and 5.6; 1024 x 58 45.7, 28.5, 20.9 and 18.6.
+struct LoadSplit {
+  int waves, run;
+};
+
+static LoadSplit load_split(int32_t P, int32_t L) {
+  const int64_t rows = static_cast<int64_t>(P) * L;
+  if (rows <= 2048) return LoadSplit{4, 4};
+  const int64_t run = rows / 512 / kLoadWaves * kLoadWaves;
+  return LoadSplit{kLoadWaves, static_cast<int>(std::max<int64_t>(kLoadWaves, std::min<int64_t>(64, run)))};
+}
 
 size_t eval_workspace(int64_t n_tokens, int32_t L, int32_t E, int32_t G, int32_t P, int32_t F) {
   size_t used = 0;
@@ -1143,7 +1158,8 @@ int launch_eval(const int16_t* trace, int64_t N, int32_t L, int32_t K, int32_t E
     if (rc != TACG_OK) return rc;
     if (hipGetLastError() != hipSuccess) return TACG_E_DEVICE;
   }
-  hipLaunchKernelGGL(ev_finalize, dim3((P + kLoadRun - 1) / kLoadRun, L), dim3(64 * kLoadWaves), 0, stream, a, cost_home,
+  const LoadSplit ls = load_split(P, L);
+  hipLaunchKernelGGL(ev_finalize, dim3((P + ls.run - 1) / ls.run, L), dim3(64 * ls.waves), 0, stream, a, ls.run, cost_home,
                      cost_span, load, cost_home_fam);
   if (stats != nullptr)
     hipLaunchKernelGGL(ev_stats, dim3(P, F), dim3(1024), 0, stream, a, stats->span_fam, stats->cross_fam,
@@ -1153,8 +1169,9 @@ int launch_eval(const int16_t* trace, int64_t N, int32_t L, int32_t K, int32_t E
 
 int launch_placement_load(const uint32_t* D, int32_t F, int32_t L, int32_t E, const uint8_t* primary, int32_t P,
                           int32_t G, int64_t* load_ref, uint32_t* d_err, hipStream_t stream) {
-  hipLaunchKernelGGL(placement_load_kernel, dim3((P + kLoadRun - 1) / kLoadRun, L), dim3(64 * kLoadWaves), 0, stream, D, F, L,
-                     E, primary, P, G, load_ref, d_err);
+  const LoadSplit ls = load_split(P, L);
+  hipLaunchKernelGGL(placement_load_kernel, dim3((P + ls.run - 1) / ls.run, L), dim3(64 * ls.waves), 0, stream, D, F, L, E,
+                     primary, P, G, ls.run, load_ref, d_err);
   return hipGetLastError() == hipSuccess ? TACG_OK : TACG_E_DEVICE;
 }
 
