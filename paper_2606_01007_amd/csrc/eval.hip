@@ -861,7 +861,7 @@ __global__ __launch_bounds__(64 * kLoadWaves) void ev_finalize(EvBase a, int run
 // App. C statistics per (placement, family): home-family dispatch mass = dispatches of the family's
 // tokens to single-candidate experts whose primary lies in the family's band (from the per-family
 // dispatch counts) + replicated-slot choices inside the band (counted by ev_main).
-// grid (P, F), 1024 threads.
+// grid (P, F), up to 1024 threads.
 __global__ __launch_bounds__(1024) void ev_stats(EvArgs a, uint64_t* __restrict__ span_fam,
                                                 uint64_t* __restrict__ cross_fam, uint64_t* __restrict__ hmass_fam) {
   __shared__ unsigned long long red[16];
@@ -885,7 +885,7 @@ __global__ __launch_bounds__(1024) void ev_stats(EvArgs a, uint64_t* __restrict_
   if (threadIdx.x == 0) {
     const int64_t pf = static_cast<int64_t>(p) * a.F + f, fp = static_cast<int64_t>(f) * a.P + p;
     unsigned long long t = 0;
-    for (int w = 0; w < 16; ++w) t += red[w];
+    for (int w = 0; w < static_cast<int>(blockDim.x >> 6); ++w) t += red[w];
     hmass_fam[pf] = t + a.ws.acc_hmass_fam[fp];
     span_fam[pf] = a.ws.acc_span_fam[fp];
     cross_fam[pf] = a.ws.acc_cross_fam[fp];
@@ -1161,8 +1161,10 @@ int launch_eval(const int16_t* trace, int64_t N, int32_t L, int32_t K, int32_t E
   const LoadSplit ls = load_split(P, L);
   hipLaunchKernelGGL(ev_finalize, dim3((P + ls.run - 1) / ls.run, L), dim3(64 * ls.waves), 0, stream, a, ls.run, cost_home,
                      cost_span, load, cost_home_fam);
+  // four entries of (layer, expert) a thread: with idle waves a short table's launch takes longer (1024 placements x 16 families
+  // of 2 x 160 entries: 57 us with 1024 threads)
   if (stats != nullptr)
-    hipLaunchKernelGGL(ev_stats, dim3(P, F), dim3(1024), 0, stream, a, stats->span_fam, stats->cross_fam,
+    hipLaunchKernelGGL(ev_stats, dim3(P, F), dim3(std::min(1024, (L * E + 255) / 256 * 64)), 0, stream, a, stats->span_fam, stats->cross_fam,
                        stats->home_mass_fam);
   return hipGetLastError() == hipSuccess ? TACG_OK : TACG_E_DEVICE;
 }
