@@ -335,9 +335,12 @@ __global__ __launch_bounds__(256) void ev_repinfo(EvBase a) {
 }
 
 // ev_zero, ev_flags, ev_replist and ev_repinfo in one launch, a workgroup per layer: all but the clearing is per layer.
-// For short tables only, where four launches cost more than the passes: at kPrepTables entries per layer a workgroup
-// takes about as long as they do.  grid (L), 256 threads.
-constexpr int64_t kPrepTables = 8192;
+// For short tables only, where four launches cost more than the passes: a workgroup takes kPrepTables entries per layer about
+// as long as they do, and with secondaries kPrepPlace placements, whose candidate sets it works through sixteen at a time.
+// Whole scoring calls, four launches / one, at 12 layers x 1000 tokens, top-2: E = 128 without secondaries 23.2 / 20.4 us
+// at 8 placements, 25.3 / 25.1 at 32, 24.6 / 27.6 at 64; with 6 x 3 replicas 33.3 / 26.7, 37.3 / 37.6 and 38.0 / 48.9; E = 16 with
+// 6 x 3 replicas 32.3 / 25.0 at 16 (E = 8), 38.5 / 40.0 at 128, 71 / 103 at 512.  grid (L), 256 threads.
+constexpr int64_t kPrepTables = 4096, kPrepPlace = 64;
 
 template <int R>
 __global__ __launch_bounds__(256) void ev_prep(EvBase a) {
@@ -1111,7 +1114,7 @@ int launch_eval(const int16_t* trace, int64_t N, int32_t L, int32_t K, int32_t E
 
   const EvBase& base = a;
   const dim3 block(256);
-  if (static_cast<int64_t>(P) * E <= kPrepTables) {
+  if (static_cast<int64_t>(P) * E <= kPrepTables && (R == 0 || P <= kPrepPlace)) {
     switch (R) {
       case 0: hipLaunchKernelGGL(ev_prep<0>, dim3(L), block, 0, stream, base); break;
       case 1: hipLaunchKernelGGL(ev_prep<1>, dim3(L), block, 0, stream, base); break;

@@ -27,6 +27,12 @@ def _gpu():
     (256, 1, 3, [700, 0, 1, 2000], 8, 10, 2, 4),
     (16, 6, 2, [0, 1, 0], 6, 3, 0, 0),
     (40, 3, 58, [5, 70], 9, 5, 1, 3),
+    # one preparation launch up to 4096 table entries a layer, with secondaries up to 64 placements
+    (64, 4, 2, [200], 9, 64, 2, 6),
+    (64, 4, 2, [200], 9, 65, 2, 6),
+    (32, 3, 2, [100, 50], 12, 65, 1, 4),
+    (32, 3, 3, [100, 50], 12, 128, 0, 0),
+    (32, 3, 3, [100, 50], 12, 129, 0, 0),
 ])
 def test_short(E, k, L, counts, G, P, R, n_rep):
     print(f"short E={E} k={k} L={L} F={len(counts)} N={sum(counts)} G={G} P={P} R={R}x{n_rep}", flush=True)
