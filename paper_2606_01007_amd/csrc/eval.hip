@@ -1138,8 +1138,10 @@ int launch_eval(const int16_t* trace, int64_t N, int32_t L, int32_t K, int32_t E
   }
   if (hipGetLastError() != hipSuccess) return TACG_E_DEVICE;
   if (np > 0) {
+    int32_t with_tokens = 0;
+    for (int f = 0; f < F; ++f) with_tokens += fam_off_host[f + 1] > fam_off_host[f];
     const bool planes = stats == nullptr && eval_uses_planes(K, E, G);
-    const bool tokens = eval_uses_tokens(P, R, planes);
+    const bool tokens = eval_uses_tokens(P, R, planes, N, L, K, with_tokens);
     CountSegs segs;
     for (int f = 0; f < TACG_MAX_FAMILIES; ++f)
       segs.end[f] = f < F ? static_cast<uint32_t>(fam_off_host[f + 1]) : 0xffffffffu;

@@ -134,8 +134,18 @@ int launch_eval_planes(const EvBase& e, const int64_t* fam_off_host, const int32
 // tokens x 16 layers), lane = token against lane = placement: E = 256, 32 GPUs, 16 x 3 replicas 204 / 312 us at 24
 // placements, 242 / 312 at 32, 358 / 309 at 48; E = 128, 16 GPUs, no replicas 126 / 188 us at 48, 135 / 190 at 64; against
 // bit planes (E = 128, 8 GPUs, 8 x 2 replicas) 63 / 84 us at 4, 86 / 85 at 8, 137 / 89 at 16.
-inline bool eval_uses_tokens(int32_t n_place, int32_t n_sec, bool planes) {
-  return n_place <= (planes ? 6 : n_sec > 0 ? 40 : 64);
+//
+// A workgroup of lane = token scores four placements of one family's chunk, so from more than 24 placements on the set-up of
+// its many workgroups (about 8.5 ns of the full chip each, against 50 ns for one of lane = placement) needs token-layers
+// to pay for it, unless two rounds of workgroups hold them all (four with secondaries).  64 families, lane = token against lane = placement:
+// E = 96, top-2, 64 placements, 58 layers x 356 tokens a family 550 / 185 us; E = 65, top-12, 32 placements, 24 layers x 10
+// tokens 152 / 63 us; E = 64, top-6, 40 placements, 24 layers x 687 tokens 151 / 210 us; E = 192, top-16, 40 placements, 8 layers
+// x 1612 tokens 173 / 307 us; 24 placements at most 19 / 18 us at any length.
+inline bool eval_uses_tokens(int32_t n_place, int32_t n_sec, bool planes, int64_t n_tokens, int32_t n_layers, int32_t top_k,
+                             int32_t families_with_tokens) {
+  if (n_place > (planes ? 6 : n_sec > 0 ? 40 : 64)) return false;
+  const int64_t fam = families_with_tokens > 0 ? families_with_tokens : 1;
+  return n_place <= 24 || (n_place + 3) / 4 * fam * n_layers <= (n_sec > 0 ? 4096 : 2048) || n_tokens / fam * top_k >= 4096;
 }
 int launch_eval_tokens(const EvBase& e, const int64_t* fam_off_host, const int32_t* home_start_host,
                        const int32_t* home_size_host, hipStream_t stream);

@@ -33,6 +33,14 @@ def _gpu():
     (32, 3, 2, [100, 50], 12, 65, 1, 4),
     (32, 3, 3, [100, 50], 12, 128, 0, 0),
     (32, 3, 3, [100, 50], 12, 129, 0, 0),
+    # lane = token from 25 placements on: token-layers enough, or few workgroups (2048; 4096 with secondaries)
+    (48, 2, 4, [40] * 64, 10, 24, 0, 0),
+    (48, 2, 4, [40] * 64, 10, 32, 0, 0),
+    (48, 2, 5, [40] * 64, 10, 28, 0, 0),
+    (20, 3, 6, [30] * 64, 12, 40, 2, 4),
+    (20, 3, 7, [30] * 64, 12, 40, 2, 4),
+    (33, 16, 9, [256] * 8, 11, 64, 0, 0),
+    (33, 16, 9, [255] * 16, 11, 64, 0, 0),
 ])
 def test_short(E, k, L, counts, G, P, R, n_rep):
     print(f"short E={E} k={k} L={L} F={len(counts)} N={sum(counts)} G={G} P={P} R={R}x{n_rep}", flush=True)
