@@ -1140,7 +1140,7 @@ int launch_eval(const int16_t* trace, int64_t N, int32_t L, int32_t K, int32_t E
   if (np > 0) {
     int32_t with_tokens = 0;
     for (int f = 0; f < F; ++f) with_tokens += fam_off_host[f + 1] > fam_off_host[f];
-    const bool planes = stats == nullptr && eval_uses_planes(K, E, G);
+    const bool planes = stats == nullptr && eval_uses_planes(K, E, G, R, N, with_tokens);
     const bool tokens = eval_uses_tokens(P, R, planes, N, L, K, with_tokens);
     CountSegs segs;
     for (int f = 0; f < TACG_MAX_FAMILIES; ++f)

@@ -125,7 +125,8 @@ struct TraceIds {
 };
 
 // The bit-plane trace pass (eval_planes.hip): whether it takes these sizes, and its launch.
-bool eval_uses_planes(int32_t top_k, int32_t n_experts, int32_t n_gpus);
+bool eval_uses_planes(int32_t top_k, int32_t n_experts, int32_t n_gpus, int32_t n_sec, int64_t n_tokens,
+                      int32_t families_with_tokens);
 int launch_eval_planes(const EvBase& e, const int64_t* fam_off_host, const int32_t* home_start_host,
                        const int32_t* home_size_host, hipStream_t stream);
 

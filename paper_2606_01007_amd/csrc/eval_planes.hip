@@ -645,10 +645,15 @@ size_t lds_k(int E, int G) {
 }  // namespace
 
 // At most 8 GPUs (a plane per GPU: the LDS reads and the planes of a token grow with their number; 8 took a third of the
-// lane = placement pass's time, see above), and the tables of all experts within the 160 KB of LDS (every size but top-9 and above
-// with more than about 200 experts).
-bool eval_uses_planes(int32_t K, int32_t E, int32_t G) {
+// lane = placement pass's time, see above), and the tables of all experts within the 160 KB of LDS: every size with at most 4
+// GPUs or top-8; with 5 to 8 GPUs up to 252 experts at top-9 and top-10, 244 at top-11 and top-12, and 236 above.
+// Not for few experts without replicas, a short choice and short families, where the other pass's tables and steps are small and a
+// class's set-up and flush are most of this one: E = 16, top-2, 512 placements, 24 layers, this pass against the other, 64 families
+// of 8 tokens 104 / 77 us, 16 of 128 58 / 48 us, 64 of 128 129 / 136 us; 2 layers, 64 families of 64 tokens 32 / 23 us (E =
+// 60, top-4: 32 / 32 us).
+bool eval_uses_planes(int32_t K, int32_t E, int32_t G, int32_t n_sec, int64_t n_tokens, int32_t families_with_tokens) {
   if (G > 8) return false;
+  if (E <= 32 && K <= 2 && n_sec == 0 && n_tokens <= int64_t(128) * families_with_tokens) return false;
   switch (K) {
 #define TACG_K(k) \
   case k:         \

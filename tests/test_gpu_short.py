@@ -41,6 +41,12 @@ def _gpu():
     (20, 3, 7, [30] * 64, 12, 40, 2, 4),
     (33, 16, 9, [256] * 8, 11, 64, 0, 0),
     (33, 16, 9, [255] * 16, 11, 64, 0, 0),
+    # bit planes or not: few experts, a short choice, no replicas, 128 tokens a family
+    (16, 2, 2, [128] * 4, 6, 520, 0, 0),
+    (16, 2, 2, [129, 128, 128], 6, 520, 0, 0),
+    (32, 1, 2, [1] * 64, 8, 97, 0, 0),
+    (33, 1, 2, [1] * 64, 8, 97, 0, 0),
+    (16, 2, 2, [100] * 4, 6, 70, 1, 2),
 ])
 def test_short(E, k, L, counts, G, P, R, n_rep):
     print(f"short E={E} k={k} L={L} F={len(counts)} N={sum(counts)} G={G} P={P} R={R}x{n_rep}", flush=True)
