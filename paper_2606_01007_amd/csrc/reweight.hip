@@ -52,7 +52,7 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
-constexpr int kSums = 8;  // values summed over the wave together, and family rows of C held by a wave
+constexpr int kSums = 8;  // values summed over the wave together, and most family rows of C held by a wave
 
 // One halving exchange between lanes 8 M apart: the lower lane keeps values 0 .. M - 1 of both, the upper one M .. 2 M - 1.
 template <int M>
@@ -101,22 +101,24 @@ __device__ __forceinline__ void family_tokens(const uint32_t* __restrict__ D, in
   }
 }
 
-// One wave's share of the family rows of C: families f0 .. f0 + 7 (f0 = 8 wave) of a row, four columns per lane.
+// One wave's share of the family rows of C: families f0 .. f0 + U - 1 (f0 = 8 wave) of a row, four columns per lane.  U = 2 or
+// 4 for at most so many families in all (E = 256, 2 families, 58 layers, GESR scores: 35.6 us with the arithmetic of eight).
+template <int U>
 struct FamRows {
-  double inv[kSums];       // 1 / N_f (0 for an empty family or past F)
+  double inv[U];           // 1 / N_f (0 for an empty family or past F)
   const uint32_t* base;    // row 0 of family f0
   int64_t stride;          // between families
   int E, n;                // n: families of this wave
-  uint32_t next[kSums][4];
+  uint32_t next[U][4];
 
   __device__ __forceinline__ void init(const uint32_t* D, const uint32_t* C, int F, int L, int E_, int k, int l, int f0) {
     const int lane = threadIdx.x & 63;
     E = E_;
-    n = min(kSums, F - f0);
+    n = min(U, F - f0);
     stride = static_cast<int64_t>(L) * E * E;
     base = C + (static_cast<int64_t>(f0) * L + l) * E * E;
 #pragma unroll
-    for (int u = 0; u < kSums; ++u) {
+    for (int u = 0; u < U; ++u) {
       const uint32_t* d = D + (static_cast<int64_t>(f0 + min(u, n - 1)) * L + l) * E;
       unsigned long long t = 0;  // an exact integer sum over the experts
 #pragma unroll
@@ -130,20 +132,20 @@ struct FamRows {
   __device__ __forceinline__ void fetch(int i) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int u = 0; u < kSums; ++u) {
+    for (int u = 0; u < U; ++u) {
       const uint32_t* row = base + min(u, n - 1) * stride + static_cast<int64_t>(i) * E;
 #pragma unroll
       for (int q = 0; q < 4; ++q) next[u][q] = row[min(lane + 64 * q, E - 1)];
     }
   }
   // the fetched rows, the diagonal and columns past E as zero
-  __device__ __forceinline__ void take(int i, uint32_t (&v)[kSums][4]) const {
+  __device__ __forceinline__ void take(int i, uint32_t (&v)[U][4]) const {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const bool on = lane + 64 * q < E && lane + 64 * q != i;
 #pragma unroll
-      for (int u = 0; u < kSums; ++u) v[u][q] = on ? next[u][q] : 0u;
+      for (int u = 0; u < U; ++u) v[u][q] = on ? next[u][q] : 0u;
     }
   }
 };
@@ -151,6 +153,7 @@ struct FamRows {
 // Workgroups of ceil(F / 8) waves, one row of A-bar at a time: every wave scales its families' rows, the waves' parts of
 // the row meet in LDS (two buffers in turn, one barrier a row), and the next row's loads are in flight meanwhile.
 // grid (L, row blocks); dynamic LDS: 2 x waves x E doubles.
+template <int U>
 __global__ __launch_bounds__(512) void rw_rows(const uint32_t* __restrict__ D, const uint32_t* __restrict__ C, int F,
                                                int L, int E, int k, int rows, RwWs ws) {
   extern __shared__ double part[];  // [2][nw][E]
@@ -158,18 +161,18 @@ __global__ __launch_bounds__(512) void rw_rows(const uint32_t* __restrict__ D, c
   const int l = blockIdx.x, nw = blockDim.x >> 6;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r0 = blockIdx.y * rows, r1 = min(E, r0 + rows);
-  FamRows fr;
+  FamRows<U> fr;
   fr.init(D, C, F, L, E, k, l, kSums * wave);
   fr.fetch(r0);
   double mx = 0.0;
   for (int i = r0; i < r1; ++i) {
-    uint32_t v[kSums][4];
+    uint32_t v[U][4];
     fr.take(i, v);
     fr.fetch(min(i + 1, E - 1));
     double* const mine = part + static_cast<size_t>(((i & 1) * nw + wave)) * E;
-    double x[kSums], ab[4] = {0, 0, 0, 0};
+    double x[kSums] = {}, ab[4] = {0, 0, 0, 0};
 #pragma unroll
-    for (int u = 0; u < kSums; ++u) {
+    for (int u = 0; u < U; ++u) {
       x[u] = 0.0;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -221,7 +224,7 @@ __global__ __launch_bounds__(kPrefThreads) void rw_pref(const uint32_t* __restri
   const double* const cl = ws.c + static_cast<int64_t>(l) * F * E;
   family_tokens(D, F, L, E, k, l, inv_n, nf);
   if (wave == 0) {
-    const double m = wave_max(lane < row_blocks ? sl[lane] : 0.0);  // at most E / 4 <= 64 row blocks
+    const double m = wave_max(lane < row_blocks ? sl[lane] : 0.0);  // at most 64 row blocks
     if (lane == 0) ws.max[l] = m;
   }
   __syncthreads();
@@ -350,6 +353,7 @@ __global__ __launch_bounds__(256, 4) void rw_graph(int F, int L, int E, double a
 // rows in registers between A-bar and the per-family terms, so C is read once.  Bound by the read of C and the
 // float64 arithmetic; measured on MI355X at E = 256, 16 families, 58 layers: 152 -> 70 us (C read twice, a wave sum per
 // family and term).  grid (L, row blocks); dynamic LDS: 2 x waves x E doubles.
+template <int U>
 __global__ __launch_bounds__(512) void gesr_scores_kernel(const uint32_t* __restrict__ D, const uint32_t* __restrict__ C,
                                                           int F, int L, int E, int k, int rows,
                                                           double* __restrict__ cent, double* __restrict__ cons,
@@ -360,17 +364,17 @@ __global__ __launch_bounds__(512) void gesr_scores_kernel(const uint32_t* __rest
   const int l = blockIdx.x, nw = blockDim.x >> 6;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r0 = blockIdx.y * rows, r1 = min(E, r0 + rows);
-  FamRows fr;
+  FamRows<U> fr;
   fr.init(D, C, F, L, E, k, l, kSums * wave);
   fr.fetch(r0);
   for (int i = r0; i < r1; ++i) {
-    uint32_t v[kSums][4];
+    uint32_t v[U][4];
     fr.take(i, v);
     fr.fetch(min(i + 1, E - 1));
     double* const mine = part + static_cast<size_t>(((i & 1) * nw + wave)) * E;
     double ab[4] = {0, 0, 0, 0};
 #pragma unroll
-    for (int u = 0; u < kSums; ++u)
+    for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int q = 0; q < 4; ++q) ab[q] += v[u][q] * fr.inv[u];
 #pragma unroll
@@ -390,9 +394,9 @@ __global__ __launch_bounds__(512) void gesr_scores_kernel(const uint32_t* __rest
       nb2 += ab[q] * ab[q];
     }
     const double nb = sqrt(wave_sum(nb2));
-    double dot[kSums], na2[kSums], dev2[kSums];
+    double dot[kSums] = {}, na2[kSums] = {}, dev2[kSums] = {};
 #pragma unroll
-    for (int u = 0; u < kSums; ++u) {
+    for (int u = 0; u < U; ++u) {
       dot[u] = na2[u] = dev2[u] = 0.0;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -444,12 +448,15 @@ size_t reweight_workspace(int32_t F, int32_t L, int32_t E) {
   return used;
 }
 
-// Rows per workgroup of the row passes: about as many waves as the chip holds at three per SIMD, so that they run in
-// one round (16 rows left it at 1.8 waves per SIMD at 256 experts, 16 families, 58 layers; 8 rows made a round and a
-// quarter); at least four, so that N_f is not summed again for every few rows.
+// Rows per workgroup of the row passes: as few as leave no more workgroups than the chip holds at once at three waves per SIMD
+// (a workgroup's rows are a chain; at 256 experts, 16 families, 58 layers 16 rows left the chip at 1.8 waves per SIMD and 8 made
+// a round and a quarter), 16 at most.  GESR scores at 1, 2 and 4 rows: E = 8, 2 families, 24 layers 7.8, 9.9 and 15.0 us; E =
+// 128, 16 families, 12 layers 12.7, 13.8 and 21.0; E = 256, 64 families, 4 layers (the chip full at 4) 43.6, 43.6 and 30.9.
 static int rows_per_block(int L, int E, int nw) {
-  const int64_t waves = 3 * 4 * 256;
-  return static_cast<int>(std::max<int64_t>(4, std::min<int64_t>(kRows, (static_cast<int64_t>(L) * E * nw + waves - 1) / waves)));
+  const int64_t held = 256 * std::max(1, 12 / nw);
+  int rows = 1;
+  while (rows < kRows && static_cast<int64_t>(L) * ((E + rows - 1) / rows) > held) ++rows;
+  return rows;
 }
 
 int launch_reweight(const uint32_t* D, const uint32_t* C, int32_t F, int32_t L, int32_t E, int32_t k,
@@ -461,8 +468,11 @@ int launch_reweight(const uint32_t* D, const uint32_t* C, int32_t F, int32_t L, 
   const size_t slds = plds + 8 * static_cast<size_t>(E) * sizeof(double);
   allow_lds(&rw_pref, slds);
   allow_lds(&rw_graph, plds);
-  const int nw = (F + kSums - 1) / kSums, rows = rows_per_block(L, E, nw), blocks = (E + rows - 1) / rows;
-  hipLaunchKernelGGL(rw_rows, dim3(L, blocks), dim3(64 * nw), 2 * static_cast<size_t>(nw) * E * sizeof(double), stream, D,
+  const int nw = (F + kSums - 1) / kSums;
+  const int rows = std::max(rows_per_block(L, E, nw), (E + 63) / 64);  // rw_pref reads the blocks' maxima with one wave
+  const int blocks = (E + rows - 1) / rows;
+  auto* rows_kernel = F <= 2 ? &rw_rows<2> : F <= 4 ? &rw_rows<4> : &rw_rows<kSums>;
+  hipLaunchKernelGGL(rows_kernel, dim3(L, blocks), dim3(64 * nw), 2 * static_cast<size_t>(nw) * E * sizeof(double), stream, D,
                      C, F, L, E, k, rows, ws);
   hipLaunchKernelGGL(rw_pref, dim3(L), dim3(kPrefThreads), slds, stream, D, F, L, E, k, tau, eps, blocks, pref, ws);
   hipLaunchKernelGGL(rw_graph, dim3(L, rb), dim3(256), plds, stream, F, L, E, alpha, a_tilde, a_hat, ws);
@@ -472,7 +482,8 @@ int launch_reweight(const uint32_t* D, const uint32_t* C, int32_t F, int32_t L, 
 int launch_gesr_scores(const uint32_t* D, const uint32_t* C, int32_t F, int32_t L, int32_t E, int32_t k, double* cent,
                        double* cons, double* spec, hipStream_t stream) {
   const int nw = (F + kSums - 1) / kSums, rows = rows_per_block(L, E, nw);
-  hipLaunchKernelGGL(gesr_scores_kernel, dim3(L, (E + rows - 1) / rows), dim3(64 * nw),
+  auto* kernel = F <= 2 ? &gesr_scores_kernel<2> : F <= 4 ? &gesr_scores_kernel<4> : &gesr_scores_kernel<kSums>;
+  hipLaunchKernelGGL(kernel, dim3(L, (E + rows - 1) / rows), dim3(64 * nw),
                      2 * static_cast<size_t>(nw) * E * sizeof(double), stream, D, C, F, L, E, k, rows, cent, cons, spec);
   return hipGetLastError() == hipSuccess ? TACG_OK : TACG_E_DEVICE;
 }

@@ -1,5 +1,5 @@
 """GPU parity of the passes over the family counts (reweighting, GESR scores, distances, top pairs) where their
-work split changes: one wave per eight families (1 to 64 families), sixteen rows per workgroup, 64 columns per lane step,
+work split changes: one wave per eight families (1 to 64 families; up to 2 and 4 apart), 1 to 16 rows per workgroup, 64 columns per lane step,
 rows paired from both ends of the triangle (odd and even E), and families without tokens.
 float64 results: sums of at most E F terms in another order, 2 E F 2^-53 relative to the sum of magnitudes, and a square
 root; float32 results: one rounding (2^-24) of values whose z-scores lose at most about 1e4 x 2^-53."""
@@ -35,7 +35,8 @@ def _counts(F, L, E, k, seed, empty):
 @pytest.mark.parametrize("F,L,E,k,empty", [
     (2, 2, 3, 2, ()), (8, 1, 16, 4, ()), (9, 2, 17, 3, (8,)), (16, 2, 64, 6, (0, 9)), (17, 1, 65, 8, ()),
     (24, 2, 128, 8, ()), (33, 1, 130, 5, (32,)), (64, 1, 40, 4, ()), (3, 2, 255, 8, ()), (16, 1, 256, 8, ()),
-    (1, 2, 70, 4, ()),
+    (1, 2, 70, 4, ()), (2, 1, 256, 8, ()), (2, 13, 255, 4, ()), (3, 40, 64, 4, (1,)), (4, 1, 129, 6, ()), (5, 12, 129, 6, (0,)),
+    (9, 30, 8, 2, ()),
 ])
 def test_family_passes(F, L, E, k, empty):
     print(f"families F={F} L={L} E={E} k={k} empty={empty}", flush=True)
