@@ -20,6 +20,7 @@
 //   * At E <= 64 with k >= 4, and at E <= 128 with 8 <= k <= 12, the partial slots come from 4-bit
 //     matrix products instead (coact_mfma.hip), with the same split of x, the same slots and the
 //     same reduction.
+#include <algorithm>
 #include <cmath>
 
 #include "tacg_internal.h"
@@ -409,16 +410,21 @@ size_t coact_bins(int32_t n_experts, int32_t top_k) {
   return static_cast<size_t>(n_experts) * static_cast<size_t>(n_experts - 1) / 2;
 }
 
-// Counting takes total x a / W, and the reduction of a segment W / segments + 1 slots of b each, one after the other: their
-// sum is least at W = sqrt(total x segments x a / b).  Measured on MI355X: a = 0.3 + 0.03 k (k - 1) ns per token-layer
-// (matrix path: 3.5 ns at E <= 64, 8 ns above), b = 0.15, 0.32, 0.72 and 1.28 us per slot at up to 64, 128, 192 and 256
-// experts.  Without this limit, one segment took, per call: E = 256, top-2, 374006 tokens 374 us with 256 workgroups against 40
-// with 8; E = 160, top-6, 200000 tokens 234 against 40 with 16; E = 64, top-8, 2 layers x 500000 tokens 112 against 55 with 128.
+// With W workgroups counting takes (total x a + segments x d) / W (d: a workgroup stores and clears its counts at the end of a
+// segment), the reduction of a segment W / segments + 1 slots of b each, one after the other, and all slots W x c of the
+// chip's time: the sum is least at W = sqrt((total x a + segments x d) / (b / segments + c)).  Measured on MI355X: a = 0.3 + 0.03 k
+// (k - 1) ns per token-layer (matrix path: 3.5 ns at E <= 64, 8 ns above, d and c not visible), b = 0.15, 0.32, 0.72 and
+// 1.28 us, d about 1, 2.5, 4 and 6 us, c 8, 15, 20 and 26 ns at up to 64, 128, 192 and 256 experts.  Without this limit, one
+// segment took, per call: E = 256, top-2, 374006 tokens 374 us with 256 workgroups against 40 with 8; E = 160, top-6, 200000
+// tokens 234 against 40 with 16; E = 64, top-8, 2 layers x 500000 tokens 112 against 55 with 128.
 int coact_num_workgroups(int64_t total, double segments, int32_t n_experts, int32_t top_k) {
-  const int nq = (n_experts + 63) / 64;
-  const double a = coact_uses_mfma(n_experts, top_k) ? (nq == 1 ? 3.5 : 8.0) : 0.3 + 0.03 * top_k * (top_k - 1);
-  const double b = nq == 1 ? 150.0 : 80.0 * nq * nq;
-  const double best = std::sqrt(static_cast<double>(total) * segments * a / b);
+  static_assert(TACG_MAX_EXPERTS <= 256, "four classes of expert count");
+  constexpr double kSlot[4] = {150.0, 320.0, 720.0, 1280.0}, kEnd[4] = {1000.0, 2500.0, 4000.0, 6000.0}, kChip[4] = {8, 15, 20, 26};
+  const int q = std::min((n_experts - 1) / 64, 3);  // the workspace is also asked for beyond the supported sizes
+  const bool mfma = coact_uses_mfma(n_experts, top_k);
+  const double a = mfma ? (q == 0 ? 3.5 : 8.0) : 0.3 + 0.03 * top_k * (top_k - 1);
+  const double d = mfma ? 0.0 : kEnd[q], c = mfma ? 0.0 : kChip[q];
+  const double best = segments > 0 ? std::sqrt((total * a + segments * d) / (kSlot[q] / segments + c)) : 1.0;
   if (coact_uses_mfma(n_experts, top_k)) return coact_mfma_workgroups(total, best, n_experts);
   // E > 128: the triangle needs more than half of the 160 KB LDS, so one 1024-thread workgroup per
   // CU; otherwise four 512-thread workgroups per CU (the same 32 waves, with four private triangles)
