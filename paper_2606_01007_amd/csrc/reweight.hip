@@ -78,10 +78,10 @@ __device__ __forceinline__ double wave_sum8(double (&x)[kSums]) {
   return s;
 }
 
-// 1 / N_f of the layer's families (0 for an empty one) into inv_n, N_f into nf if wanted: one wave per family, an
-// exact integer sum over the experts.  The caller synchronises.
+// N_f of the layer's families into nf: one wave per family, an exact integer sum over the experts.  The caller
+// synchronises.
 __device__ __forceinline__ void family_tokens(const uint32_t* __restrict__ D, int F, int L, int E, int k, int l,
-                                              double* inv_n, double* nf) {
+                                              double* nf) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   for (int f = wave; f < F; f += nw) {
     const uint32_t* d = D + (static_cast<int64_t>(f) * L + l) * E;
@@ -93,11 +93,7 @@ __device__ __forceinline__ void family_tokens(const uint32_t* __restrict__ D, in
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) t += __shfl_xor(t, o, 64);
-    const double n = static_cast<double>(t) / k;
-    if (lane == 0) {
-      inv_n[f] = n > 0 ? 1.0 / n : 0.0;
-      if (nf) nf[f] = n;
-    }
+    if (lane == 0) nf[f] = static_cast<double>(t) / k;
   }
 }
 
@@ -214,7 +210,7 @@ __global__ __launch_bounds__(kPrefThreads) void rw_pref(const uint32_t* __restri
                                                         double tau, double eps, int row_blocks, float* __restrict__ pref,
                                                         RwWs ws) {
   extern __shared__ double sc[];
-  __shared__ double inv_n[TACG_MAX_FAMILIES], nf[TACG_MAX_FAMILIES];
+  __shared__ double nf[TACG_MAX_FAMILIES];
   double* const sum_u = sc + static_cast<size_t>(F) * E;  // [4][E], then in [0][E] the maximum over f
   double* const sum_c = sum_u + 4 * static_cast<size_t>(E);  // [4][E], then in [0][E] the softmax denominator
   const int l = blockIdx.x, tid = threadIdx.x;
@@ -222,7 +218,7 @@ __global__ __launch_bounds__(kPrefThreads) void rw_pref(const uint32_t* __restri
   constexpr int kWaves = kPrefThreads / 64;
   double* const sl = ws.s + static_cast<int64_t>(l) * F * E;
   const double* const cl = ws.c + static_cast<int64_t>(l) * F * E;
-  family_tokens(D, F, L, E, k, l, inv_n, nf);
+  family_tokens(D, F, L, E, k, l, nf);
   if (wave == 0) {
     const double m = wave_max(lane < row_blocks ? sl[lane] : 0.0);  // at most 64 row blocks
     if (lane == 0) ws.max[l] = m;
@@ -466,7 +462,7 @@ int launch_reweight(const uint32_t* D, const uint32_t* C, int32_t F, int32_t L, 
   const int rb = (E + kRows - 1) / kRows;
   const size_t plds = static_cast<size_t>(F) * E * sizeof(double);  // <= 64 x 256 x 8 = 128 KB
   const size_t slds = plds + 8 * static_cast<size_t>(E) * sizeof(double);
-  allow_lds(&rw_pref, slds);
+  allow_lds(&rw_pref, slds, TACG_MAX_FAMILIES * sizeof(double));
   allow_lds(&rw_graph, plds);
   const int nw = (F + kSums - 1) / kSums;
   const int rows = std::max(rows_per_block(L, E, nw), (E + 63) / 64);  // rw_pref reads the blocks' maxima with one wave

@@ -12,10 +12,11 @@ namespace tacg {
 // Round a byte count up to the 256-byte alignment used for every workspace sub-buffer.
 inline size_t align256(size_t x) { return (x + 255u) & ~size_t(255); }
 
-// Dynamic LDS of a launch: the runtime allows 64 KB by itself, so only more costs the call (about 1 us).
+// Dynamic LDS of a launch: the runtime allows 64 KB by itself, the kernel's static LDS among them, so only more costs the call
+// (about 1 us).
 template <class Kernel>
-inline void allow_lds(Kernel* kernel, size_t bytes) {
-  if (bytes > 65536)
+inline void allow_lds(Kernel* kernel, size_t bytes, size_t static_bytes = 0) {
+  if (bytes + static_bytes > 65536)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                               static_cast<int>(bytes));
 }

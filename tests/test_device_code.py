@@ -88,6 +88,22 @@ def test_waits_cover_the_lds_exchanges(code_objects):
     assert not found, f"{len(found)} instructions, the first: {found[:5]}"
 
 
+# static LDS that a launch with dynamic LDS above 64 KB counts in (bytes); the bit planes address theirs from 0
+STATIC_LDS = {"ev_planes": 0, "ev_main": 0, "on_main": 0, "group_objective_kernel": 0, "coact_hist_kernel": 0,
+              "coact_reduce_kernel": 0, "rw_graph": 0, "rw_pref": 512}
+
+
+def test_static_lds_is_what_the_launches_assume(code_objects):
+    seen = {}
+    for path in code_objects:
+        for m in re.finditer(r"\.group_segment_fixed_size:\s*(\d+)(?:(?!\.group_segment_fixed_size).)*?\.name:\s*(\S+)",
+                             _tool("llvm-readelf", "--notes", path), re.S):
+            for name in STATIC_LDS:
+                if re.search(rf"\d{name}(?![a-z_])", m.group(2)):
+                    seen.setdefault(name, set()).add(int(m.group(1)))
+    assert seen == {name: {size} for name, size in STATIC_LDS.items()}
+
+
 def test_the_check_of_waits_sees_a_missing_one():
     head = "0000000000001000 <k>:\n\tds_wrxchg2st64_rtn_b32 v[2:3], v9, v1, v1 offset1:1\n\tds_add_u32 v9, v8\n"
     use = "\tv_cvt_f64_u32_e32 v[4:5], v3\n"

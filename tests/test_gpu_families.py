@@ -36,7 +36,7 @@ def _counts(F, L, E, k, seed, empty):
     (2, 2, 3, 2, ()), (8, 1, 16, 4, ()), (9, 2, 17, 3, (8,)), (16, 2, 64, 6, (0, 9)), (17, 1, 65, 8, ()),
     (24, 2, 128, 8, ()), (33, 1, 130, 5, (32,)), (64, 1, 40, 4, ()), (3, 2, 255, 8, ()), (16, 1, 256, 8, ()),
     (1, 2, 70, 4, ()), (2, 1, 256, 8, ()), (2, 13, 255, 4, ()), (3, 40, 64, 4, (1,)), (4, 1, 129, 6, ()), (5, 12, 129, 6, (0,)),
-    (9, 30, 8, 2, ()),
+    (9, 30, 8, 2, ()), (24, 1, 256, 8, ()),  # the last: 64 KB of dynamic LDS and some static
 ])
 def test_family_passes(F, L, E, k, empty):
     print(f"families F={F} L={L} E={E} k={k} empty={empty}", flush=True)
