@@ -24,7 +24,7 @@ def _gpu():
 
 
 @pytest.mark.parametrize("E,k,counts,G,P,R,n_rep,bad", [
-    (8, 2, [64, 1, 0, 65], 4, 1, 0, 0, 0),
+    (8, 2, [640, 1, 0, 65], 4, 7, 0, 0, 0),        # the fewest placements of this pass
     (9, 1, [130], 1, 31, 0, 0, 0),
     (16, 8, [63, 200], 4, 32, 3, 16, 0),
     (24, 5, [1, 2, 3, 700], 8, 33, 4, 16, 3),
@@ -36,7 +36,15 @@ def _gpu():
     (40, 16, [257, 300], 8, 64, 4, 16, 0),
     (256, 8, [600, 600], 8, 40, 2, 16, 1),       # the largest table
     (256, 16, [300, 200], 3, 40, 2, 16, 1),
-    (256, 12, [300, 200], 8, 40, 2, 16, 0),      # too large for the LDS: the general pass
+    (248, 8, [300, 200], 8, 40, 2, 16, 0),       # 768 threads and, with one expert more, 512
+    (249, 8, [300, 200], 8, 40, 2, 16, 1),
+    (252, 10, [300, 200], 8, 40, 2, 16, 0),      # the largest tables above top-8 ...
+    (244, 11, [300, 200], 5, 40, 2, 16, 0),
+    (236, 16, [300, 200], 8, 40, 2, 16, 1),
+    (253, 9, [300, 200], 8, 40, 2, 16, 0),       # ... and the first too large for the LDS: the general pass
+    (245, 12, [300, 200], 5, 40, 2, 16, 1),
+    (237, 13, [300, 200], 8, 40, 2, 16, 0),
+    (256, 12, [300, 200], 8, 40, 2, 16, 0),
     (12, 3, [40000, 30000], 2, 700, 1, 3, 0),    # long runs
 ])
 def test_planes_parity(E, k, counts, G, P, R, n_rep, bad):
