@@ -121,9 +121,18 @@ def _trace_dims(trace: torch.Tensor):
     return trace.shape
 
 
+# The current stream's handle alone: a Stream object per call costs more than the rest of the argument list.  Not part of
+# torch's public interface, so the public call serves where they are missing.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream=None):
-    # the handle alone: a Stream object per call costs more than the rest of the argument list
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) if stream is None else stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or _device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _host_i64(x) -> np.ndarray:

@@ -326,3 +326,13 @@ def test_noalloc_argument_errors_and_scratch_limit(L):
     assert fits and fits[0] == 1900 and 2000 < fits[-1] < 2299
     assert _noalloc(L, P=fits[-1] + 1, **big) == tacg.E_SCRATCH
     assert b"no-allocation" in L.tacg_strerror(tacg.E_SCRATCH)
+
+
+def test_current_stream_without_the_private_accessors(monkeypatch):
+    """The binding reads the current stream's handle through torch's internals where they exist, else through the public call."""
+    monkeypatch.setattr(tacg.torch.cuda, "current_stream", lambda: type("S", (), {"cuda_stream": 77}))
+    for name in ("_raw_stream", "_device"):
+        with monkeypatch.context() as m:
+            m.setattr(tacg, name, None)
+            assert tacg._stream() == 77
+    assert tacg._stream(type("S", (), {"cuda_stream": 5})) == 5
