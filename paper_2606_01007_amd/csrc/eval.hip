@@ -74,7 +74,8 @@ __global__ __launch_bounds__(256) void ev_zero(EvBase a) { zero_accumulators(a);
 // flattened trace (x = l * N + t) and walks the layers (with statistics: the families of the layers) it crosses,
 // counting the dispatches of every expert in LDS.  A token-layer with an id out of range or a repeated id is flagged,
 // counted (n_bad), left out of the counts, and marks its group of 64 consecutive token-layers in bad_tiles, so that
-// ev_main checks the ids itself only in the few tiles that meet a marked group.
+// ev_main checks the ids itself only in the few tiles that meet a marked group (the other two passes check every token when any
+// is invalid).
 // Bound by the read of the trace: the LDS adds of the counts hide behind it (2^19 tokens x 58 layers, top-8: 78 us
 // without them, and 100 us with them, while they cost the trace pass of few placements a fifth of its time).
 template <int K>
@@ -863,7 +864,7 @@ __global__ __launch_bounds__(64 * kLoadWaves) void ev_finalize(EvBase a, int run
 
 // App. C statistics per (placement, family): home-family dispatch mass = dispatches of the family's
 // tokens to single-candidate experts whose primary lies in the family's band (from the per-family
-// dispatch counts) + replicated-slot choices inside the band (counted by ev_main).
+// dispatch counts) + replicated-slot choices inside the band (counted by the trace pass).
 // grid (P, F), up to 1024 threads.
 __global__ __launch_bounds__(1024) void ev_stats(EvArgs a, uint64_t* __restrict__ span_fam,
                                                 uint64_t* __restrict__ cross_fam, uint64_t* __restrict__ hmass_fam) {
@@ -1032,7 +1033,7 @@ __global__ __launch_bounds__(64) void jain_kernel(const uint32_t* __restrict__ l
 
 // Placements per workgroup of the load passes: 64 share a layer's sums, but few placements are bound by a wave's chain of them,
 // so they are spread until the chip holds about 512 workgroups.  placement_load at 8, 16, 32 and 64 per workgroup, device time in
-// us: 90 placements x 12 layers, E = 252, 3.4, 4.2, 5.3 and 7.8; 400 x 12, E = 256, 16 families, 5.1, 5.4, 5.8 and 7.6; 256 x 58
+// us: 90 placements x 12 layers, E = 252, 3.4, 4.2, 5.3 and 7.8 (3.3 at 4, one a wave); 400 x 12, E = 256, 16 families, 5.1, 5.4, 5.8 and 7.6; 256 x 58
 // 8.9, 7.0, 7.0 and 7.8; 512 x 24, E = 60, 5.5, 4.3, 4.6 and 5.6; 1024 x 58 45.7, 28.5, 20.9 and 18.6.
 struct LoadSplit {
   int waves, run;

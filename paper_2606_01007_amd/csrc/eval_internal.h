@@ -133,7 +133,8 @@ int launch_eval_planes(const EvBase& e, const int64_t* fam_off_host, const int32
 // The lane = token trace pass (eval_tokens.hip), also with the App. C statistics, and the numbers of placements it is
 // taken for.  Its time grows with the placements, the other passes' hardly do.  Measured on MI355X per call (top-8, 2^17
 // tokens x 16 layers), lane = token against lane = placement: E = 256, 32 GPUs, 16 x 3 replicas 204 / 312 us at 24
-// placements, 242 / 312 at 32, 358 / 309 at 48; E = 128, 16 GPUs, no replicas 126 / 188 us at 48, 135 / 190 at 64; against
+// placements, 242 / 312 at 32, 358 / 309 at 48; E = 128, 16 GPUs, no replicas 126 / 188 us at 48, 135 / 190 at 64 (above
+// that the crossing depends on the sizes: at 96 to 128 placements 0.3 to 2.0 times lane = placement); against
 // bit planes (E = 128, 8 GPUs, 8 x 2 replicas) 63 / 84 us at 4, 86 / 85 at 8, 137 / 89 at 16.
 //
 // A workgroup of lane = token scores four placements of one family's chunk, so from more than 24 placements on the set-up of

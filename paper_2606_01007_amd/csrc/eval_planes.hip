@@ -618,8 +618,8 @@ int launch_t(const PlArgs& a, hipStream_t stream) {
 }
 
 // Shares of a layer's tiles: workgroups of about equal work that fill whole rounds of the 256 CUs (one
-// workgroup per CU).  A workgroup's set-up and flushes cost about as much as kSetup tiles of 16 groups, so few rounds are
-// best for short inputs; from 8 rounds on the last one no longer matters.
+// workgroup per CU).  A workgroup's set-up and flushes cost about as much as kSetup tiles of 16 groups (an estimate from the
+// times of short and long inputs, not swept), so few rounds are best for short inputs; from 8 rounds on the last one no longer matters.
 int64_t shares_of(int64_t tiles, int64_t rows, int groups) {
   constexpr int64_t kCus = 256, kSetup = 24;
   const int64_t floor_shares = (tiles + kMaxTiles - 1) / kMaxTiles;

@@ -9,7 +9,7 @@
 // together, and their choices are LDS counters.  A workgroup takes a chunk of one family's tokens of one layer
 // and four placements.
 //
-// What bounds it: the LDS, whose reads go to random rows (one expert per lane).  Measured on MI355X: two
+// What bounds it, from its instructions (no counters): the LDS, whose reads go to random rows (one expert per lane).  Measured on MI355X: two
 // placements of E = 256, top-8, 32 GPUs, 16 x 3 replicas, 2^19 tokens x 58 layers with the per-token statistics:
 // 4.59 -> 0.43 ms for the whole call.
 #include "eval_internal.h"

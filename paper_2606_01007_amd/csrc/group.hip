@@ -11,7 +11,7 @@
 //      lane walks its placement's ring of e's GPU, adding the row's entries: two LDS reads and one float64
 //      add per pair, all lanes busy when the GPUs hold equally many experts.
 //   3. The waves' sums are added in wave order.
-// What bounds it: the row entries' LDS reads (random banks) and VALU issue.  Measured on MI355X at E = 256, 32 GPUs, 1024
+// What bounds it, from its instructions (no counters): the row entries' LDS reads (random banks) and VALU issue.  Measured on MI355X at E = 256, 32 GPUs, 1024
 // placements x 58 layers (1.1e8 entries), device time: 427 -> 67 us against one workgroup per (placement, layer).
 //
 // group_gather_kernel (few placements): one workgroup per (placement, layer) lists the experts of every GPU by ballots, then
@@ -254,7 +254,7 @@ int launch_group_objective(const float* a_tilde, int32_t L, int32_t E, const uin
     return hipGetLastError() == hipSuccess ? TACG_OK : TACG_E_DEVICE;
   }
   // as many placements per workgroup as still leave the chip about one workgroup per CU (a workgroup's rows of A-tilde
-  // serve all its placements)
+  // serve all its placements); 192 is three quarters of the CUs, chosen and not swept
   const int64_t sets = (P + 63) / 64;
   if ((sets + 3) / 4 * L >= 192) launch_sets<4>(a_tilde, L, E, primary, P, G, obj, d_err, stream);
   else if ((sets + 1) / 2 * L >= 192) launch_sets<2>(a_tilde, L, E, primary, P, G, obj, d_err, stream);

@@ -56,9 +56,10 @@ def _u32(t):
 
 
 def sampled_placements(P: int, n_experts: int):
-    """Placements compared with the oracle one by one.  The scoring kernel gives each lane two
-    placements (four when E <= 64) and each workgroup 64 lanes' worth, so the sample covers the first
-    and last lanes of blocks, interior lanes, every position within a lane's group and several blocks."""
+    """Placements compared with the oracle one by one.  Above 8 GPUs the scoring kernel gives
+    each lane two placements (four when E <= 64) and each workgroup 64 lanes' worth, so the sample covers the first
+    and last lanes of blocks, interior lanes, every position within a lane's group and several blocks; on bit
+    planes (at most 8 GPUs: groups of 32 placements, 512 per workgroup) it covers several bits of several groups."""
     ppl = 4 if n_experts <= 64 else 2
     pb = 64 * ppl
     want = {0, 1, 2, 3, 37, 2 * 37 + 1, pb - 2, pb - 1, pb, pb + 1, P // 2 + 5, P // 2 + 70, (3 * P) // 4 + 43,
