@@ -226,12 +226,21 @@ __global__ __launch_bounds__(kGatherThreads) void group_gather_kernel(const floa
 }
 
 // Where the gather takes over: placements x layers, by the experts per GPU (its time grows with all three, the rings' only
-// with the last until their workgroups fill the chip).  Device times on MI355X, gather / rings in us: 256 experts on 2
-// GPUs 128 / 187 at 1024 rows, 194 / 186 at 1508, 253 / 186 at 2048; on 8 GPUs 70 / 78 at 2048, 115 / 77 at 3016; on 32 GPUs
-// 46 / 48 at 3016, 68 / 48 at 6032; 64 experts on 8 GPUs 12.2 / 13.6 at 3016, 18.7 / 14.1 at 6032; 16 experts on 8 GPUs 5.7
-// / 5.1 at 2048, 7.9 / 5.2 at 3016.  One placement of 2 layers: 256 experts on 2, 8 and 32 GPUs 25 / 180, 11 / 74 and 9 / 44.
+// with the last until their workgroups fill the chip).  Device times on MI355X, gather / rings in us, 12 layers: 256 experts on
+// one GPU 287 / 305 at 1080 rows, 415 / 304 at 1560; on 4 109 / 97 at 1560; on 8 56 / 62 at 1560, 67 / 62 at 2040; on 16 45 / 45 at
+// 2580; on 32 33 / 38 at 3600, 41 / 39 at 4800 (58 layers: 35 / 39 at 3016); 128 on 2 50 / 50 at 1508; on 16 17 / 20 at 3072, 22 / 20
+// at 4800; 64 on 32 9.4 / 11.6 at 2040, 12.0 / 11.7 at 2580; 33 on one 9.0 / 11.2 at 2040, 13.3 / 11.1 at 2580; 16 on 4 4.7 /
+// 5.0 at 2040, 6.1 / 4.7 at 2580.  One placement of 2 layers: 256 experts on 2, 8 and 32 GPUs 25 / 180, 11 / 74 and 9 / 44.
 bool group_uses_gather(int64_t rows, int E, int G) {
-  return rows <= (E >= 64 && E <= 8 * G ? 3072 : E <= 32 * G ? 2048 : 1536);
+  int64_t limit = 2432;                 // fewer than four experts per GPU
+  if (E < 32) limit = 2048;
+  else if (E < 40 && E > 8 * G) limit = 2240;
+  else if (E > 64 * G) limit = 1152;
+  else if (E > 32 * G) limit = 1408;
+  else if (E > 16 * G) limit = 1856;
+  else if (E > 8 * G) limit = 2560;
+  else if (E >= 4 * G) limit = 3456;
+  return rows <= limit;
 }
 
 template <int kSets>

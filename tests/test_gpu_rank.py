@@ -1,8 +1,8 @@
 """GPU parity of the grouping objective and the snapshot loads at the edges of their work split: one, two and four
 sets of 64 placements per workgroup, partial sets, dword-aligned and unaligned placement rows, one GPU holding
 every expert and GPUs holding one, more placements than a workgroup's run, and the numbers of placements and layers on
-both sides of the change between the objective's two kernels (1536, 2048 and 3072 by the experts per GPU), and of the runs of
-placements that the loads take (4, 8 and up to 64 a workgroup).
+both sides of the change between the objective's two kernels (1152 to 3456 by the experts per GPU), and of the runs of placements
+that the loads take (4, 8 and up to 64 a workgroup).
 Loads are whole numbers.  The objective is a float64 sum of n = E^2 non-negative terms at most: two orders of it
 differ by at most 2 n 2^-53 relative."""
 import numpy as np
@@ -26,7 +26,10 @@ def _gpu():
     (1, 1, 1, 1, 0), (3, 2, 63, 2, 0), (4, 4, 64, 3, 0), (16, 1, 65, 2, 0), (16, 16, 130, 3, 1), (20, 3, 257, 100, 0),
     (6, 5, 257, 100, 0), (64, 8, 200, 96, 0), (60, 7, 129, 2, 3), (255, 32, 70, 2, 0), (256, 32, 300, 3, 0), (256, 1, 5, 1, 2),
     (256, 32, 1536, 2, 0), (256, 32, 1537, 2, 0), (252, 8, 2048, 1, 0), (252, 8, 2049, 1, 1), (255, 2, 768, 2, 0),
-    (256, 2, 769, 2, 0), (4, 4, 1025, 2, 0), (40, 8, 300, 17, 0), (252, 4, 70, 12, 0), (16, 4, 1024, 40, 0), (3, 1, 2050, 1, 0), (33, 32, 500, 60, 0), (72, 9, 500, 60, 3),
+    (256, 2, 769, 2, 0), (4, 4, 1025, 2, 0),
+    (3, 1, 2050, 1, 0), (33, 32, 500, 60, 0), (72, 9, 500, 60, 3), (40, 8, 300, 17, 0), (252, 4, 70, 12, 0), (16, 4, 1024, 40, 0),
+    (255, 2, 576, 2, 0), (255, 2, 577, 2, 0), (80, 2, 704, 2, 0), (80, 2, 705, 2, 0), (252, 8, 1857, 1, 1), (100, 9, 2561, 1, 0),
+    (256, 32, 1728, 2, 0), (256, 32, 1729, 2, 0), (33, 16, 2433, 1, 0), (36, 4, 2241, 1, 0),
 ])
 def test_objective_and_loads(E, G, P, L, shift):
     print(f"rank E={E} G={G} P={P} L={L} shift={shift}", flush=True)
