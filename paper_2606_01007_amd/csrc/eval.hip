@@ -990,6 +990,34 @@ __global__ __launch_bounds__(64 * kLoadWaves) void placement_load_kernel(const u
   if (err) atomicOr(d_err, err);
 }
 
+// Few placements: one workgroup per placement and layer, a thread per expert.  Up to kLoadFew of them nothing is worth sharing:
+// placement_load, this / the kernel above at its best run, in us: 90 placements x 12 layers, E = 252, 2.8 / 3.3; 198 x 2, E =
+// 128, 2.4 / 2.8; one GPU holding 252 experts, 35 x 1, 3.9 / 4.5; but 100 x 24, E = 256, 16 families, 5.9 / 4.6.
+// grid (P, L), 256 threads.
+constexpr int64_t kLoadFew = 1152;
+
+__global__ __launch_bounds__(256) void placement_load_few_kernel(const uint32_t* __restrict__ D, int F, int L, int E,
+                                                                 const uint8_t* __restrict__ primary, int G,
+                                                                 int64_t* __restrict__ load_ref, uint32_t* d_err) {
+  __shared__ unsigned long long acc[TACG_MAX_GPUS];
+  const int p = blockIdx.x, l = blockIdx.y, tid = threadIdx.x;
+  if (tid < G) acc[tid] = 0;
+  __syncthreads();
+  if (tid < E) {
+    const uint32_t g = primary[(static_cast<int64_t>(p) * L + l) * E + tid];
+    if (g < static_cast<uint32_t>(G)) {
+      unsigned long long s = 0;
+#pragma unroll 8
+      for (int f = 0; f < F; ++f) s += D[(static_cast<int64_t>(f) * L + l) * E + tid];
+      if (s) __hip_atomic_fetch_add(&acc[g], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    } else {
+      atomicOr(d_err, TACG_ERR_TABLE);
+    }
+  }
+  barrier_after_lds_atomics();
+  if (tid < G) load_ref[(static_cast<int64_t>(p) * L + l) * G + tid] = static_cast<int64_t>(acc[tid]);
+}
+
 // Jain and MaxVio.  One wave per output row; lanes over GPUs.
 __global__ __launch_bounds__(64) void jain_kernel(const uint32_t* __restrict__ load, int P, int L, int G,
                                                   int per_layer, float* __restrict__ jain, float* __restrict__ maxvio) {
@@ -1177,6 +1205,10 @@ int launch_eval(const int16_t* trace, int64_t N, int32_t L, int32_t K, int32_t E
 
 int launch_placement_load(const uint32_t* D, int32_t F, int32_t L, int32_t E, const uint8_t* primary, int32_t P,
                           int32_t G, int64_t* load_ref, uint32_t* d_err, hipStream_t stream) {
+  if (static_cast<int64_t>(P) * L <= kLoadFew) {
+    hipLaunchKernelGGL(placement_load_few_kernel, dim3(P, L), dim3(256), 0, stream, D, F, L, E, primary, G, load_ref, d_err);
+    return hipGetLastError() == hipSuccess ? TACG_OK : TACG_E_DEVICE;
+  }
   const LoadSplit ls = load_split(P, L);
   hipLaunchKernelGGL(placement_load_kernel, dim3((P + ls.run - 1) / ls.run, L), dim3(64 * ls.waves), 0, stream, D, F, L, E,
                      primary, P, G, ls.run, load_ref, d_err);

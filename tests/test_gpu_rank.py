@@ -2,7 +2,7 @@
 sets of 64 placements per workgroup, partial sets, dword-aligned and unaligned placement rows, one GPU holding
 every expert and GPUs holding one, more placements than a workgroup's run, and the numbers of placements and layers on
 both sides of the change between the objective's two kernels (1152 to 3456 by the experts per GPU), and of the runs of placements
-that the loads take (4, 8 and up to 64 a workgroup).
+that the loads take (1 up to 1152 in all, then 4, 8 and up to 64 a workgroup).
 Loads are whole numbers.  The objective is a float64 sum of n = E^2 non-negative terms at most: two orders of it
 differ by at most 2 n 2^-53 relative."""
 import numpy as np
