@@ -9,8 +9,8 @@
 //   n-th largest positive count T is found by bisection in one wave, first over the threads' maxima (a lower
 //   bound), then over the list of the counts at or above that bound; pairs above T are kept, ties at T in increasing pair order until n are chosen: the rows' counts of
 //   both are prefix-summed, which gives every row its ties to keep and its first output slot, and
-//   ballots give the order within a row.  Bound, by its steps (no counters), by the read of the triangle (rows of C) and the
-//   latency of the steps; two workgroups per CU.  Measured on MI355X at E = 256, 16 families, 58 layers, n = 64:
+//   ballots give the order within a row.  Bound, by counters, by latency, that of the triangle's read (rows of C) and of
+//   the steps between barriers (the waves wait 77 % of their time; VALU 21 % busy); two workgroups per CU.  Measured on MI355X at E = 256, 16 families, 58 layers, n = 64:
 //   277 -> 73 us (the triangle staged in 130 KB of LDS and scanned there, one workgroup per CU).
 // jaccard_kernel: one wave per (layer, unordered family pair); every element of one sorted list is looked up
 //   in the other by bisection.

@@ -347,7 +347,7 @@ __global__ __launch_bounds__(256, 4) void rw_graph(int F, int L, int E, double a
 // Cent = sum_j A-bar(i, j); Cons = mean_f cos(A_f(i, :), A-bar(i, :)) (0 for a zero row);
 // Spec = max_f ||A_f(i, :) - A-bar(i, :)||_2.  The waves share a row as in rw_rows: a wave keeps its eight families'
 // rows in registers between A-bar and the per-family terms, so C is read once.  Bound by the read of C (243 MB
-// take 57 us here) and, by their count, the float64 operations; measured on MI355X at E = 256, 16 families, 58 layers: 152 -> 70 us (C read twice, a wave sum per
+// take 57 us here; by counters the waves wait 34 % of their time and the VALU is 51 % busy); measured on MI355X at E = 256, 16 families, 58 layers: 152 -> 70 us (C read twice, a wave sum per
 // family and term).  grid (L, row blocks); dynamic LDS: 2 x waves x E doubles.
 template <int U>
 __global__ __launch_bounds__(512) void gesr_scores_kernel(const uint32_t* __restrict__ D, const uint32_t* __restrict__ C,
