@@ -678,20 +678,6 @@ int launch_eval_planes(const EvBase& e, const int64_t* fam_off_host, const int32
   a.F = e.F;
   a.G = e.G;
   a.P = e.P;
-  // placement blocks: 16 groups each, the rest in powers of two (a block of 2^b groups steps 64 / 2^b tokens
-  // at once; a remainder of more than three quarters of a power of two is cheaper as one padded block)
-  const int groups = (e.P + 31) / 32;
-  a.n_full = groups / kCols;
-  a.n_pblocks = a.n_full;
-  for (int at = a.n_full * kCols, rest = groups % kCols; rest > 0;) {
-    int sz = 1;
-    while (sz < rest) sz *= 2;
-    if (sz != rest && 4 * rest <= 3 * sz) sz /= 2;
-    a.tail[a.n_pblocks - a.n_full] = static_cast<uint32_t>(at) | (static_cast<uint32_t>(sz) << 24);
-    ++a.n_pblocks;
-    at += sz;
-    rest -= std::min(sz, rest);
-  }
   int64_t tiles = 0;
   for (int f = 0; f < e.F; ++f) {
     const int64_t n = fam_off_host[f + 1] - fam_off_host[f];
@@ -704,6 +690,25 @@ int launch_eval_planes(const EvBase& e, const int64_t* fam_off_host, const int32
   for (int f = e.F; f <= TACG_MAX_FAMILIES; ++f) a.fam[f] = FamRec{0u, 0u, 0xffffffffu, 1u << 8};
   if (tiles == 0) return TACG_OK;
   if (tiles >= 0xffffffffll) return TACG_E_UNSUPPORTED;
+  // placement blocks: 16 groups each, the rest in one block padded to a power of two (a block of 2^b groups steps 64 / 2^b
+  // tokens at once).  Every block prepares all tokens and builds its own tables, so splitting the rest into smaller powers of
+  // two only pays where few layers or tiles leave the chip idle (then a remainder of up to three quarters of a power of
+  // two is split).  Whole calls, split / padded: E = 65, top-8, 64 families, 24 layers, 65 placements 102 / 70 us at 8 tokens a
+  // family, 183 / 127 at 400; E = 128, top-8, 48 layers x 65536 tokens 300 / 213 at 65, 534 / 492 at 340, 745 / 769 at 577; E = 256, top-8,
+  // 20 layers x 65536 633 / 468 at 700; but E = 100, top-10, 4 layers x 6000 tokens 68 / 87 at 384, E = 60, 2 layers x 120007 70 / 82.
+  const bool full = e.L >= 16 && tiles * e.L >= 768;
+  const int groups = (e.P + 31) / 32;
+  a.n_full = groups / kCols;
+  a.n_pblocks = a.n_full;
+  for (int at = a.n_full * kCols, rest = groups % kCols; rest > 0;) {
+    int sz = 1;
+    while (sz < rest) sz *= 2;
+    if (sz != rest && 4 * rest <= 3 * sz && !full) sz /= 2;
+    a.tail[a.n_pblocks - a.n_full] = static_cast<uint32_t>(at) | (static_cast<uint32_t>(sz) << 24);
+    ++a.n_pblocks;
+    at += sz;
+    rest -= std::min(sz, rest);
+  }
   a.n_tiles = static_cast<uint32_t>(tiles);
   a.n_shares = static_cast<int32_t>(shares_of(tiles, static_cast<int64_t>(e.L) * a.n_pblocks, std::min(groups, kCols)));
   switch (e.K) {

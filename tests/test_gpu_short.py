@@ -47,6 +47,13 @@ def _gpu():
     (32, 1, 2, [1] * 64, 8, 97, 0, 0),
     (33, 1, 2, [1] * 64, 8, 97, 0, 0),
     (16, 2, 2, [100] * 4, 6, 70, 1, 2),
+    # the last block of placements in one piece, padded: 16 layers and 768 tiles of work; split below that
+    (40, 5, 16, [9] * 48, 8, 65, 2, 5),
+    (40, 5, 15, [9] * 48, 8, 65, 2, 5),
+    (40, 5, 16, [9] * 47, 8, 160, 2, 5),
+    (20, 3, 20, [70] * 40, 3, 340, 1, 4),
+    (24, 4, 16, [40] * 50, 5, 577, 0, 0),
+    (24, 4, 16, [500] * 3, 5, 300, 3, 6),
 ])
 def test_short(E, k, L, counts, G, P, R, n_rep):
     print(f"short E={E} k={k} L={L} F={len(counts)} N={sum(counts)} G={G} P={P} R={R}x{n_rep}", flush=True)
