@@ -410,21 +410,24 @@ size_t coact_bins(int32_t n_experts, int32_t top_k) {
   return static_cast<size_t>(n_experts) * static_cast<size_t>(n_experts - 1) / 2;
 }
 
-// With W workgroups counting takes (total x a + segments x d) / W (d: a workgroup stores and clears its counts at the end of a
-// segment), the reduction of a segment W / segments + 1 slots of b each, one after the other, and all slots W x c of the
-// chip's time: the sum is least at W = sqrt((total x a + segments x d) / (b / segments + c)).  Measured on MI355X: a = 0.3 + 0.03 k
-// (k - 1) ns per token-layer (matrix path: 3.5 ns at E <= 64, 8 ns above, d and c not visible), b = 0.15, 0.32, 0.72 and
-// 1.28 us, d about 1, 2.5, 4 and 6 us, c 8, 15, 20 and 26 ns at up to 64, 128, 192 and 256 experts.  Without this limit, one
+// With W workgroups counting takes (total x a + ends x d) / W (d: a workgroup stores and clears its counts at the end of a
+// segment), the reduction of the longest segment W / longest + 1 slots of b each, one after the other (longest: the trace in
+// lengths of it), and all slots W x c of the chip's time: the sum is least at W = sqrt((total x a + ends x d) / (b / longest + c)).
+// Measured on MI355X, in ns: a = 0.3 + 0.03 k (k - 1) per token-layer (matrix path: 3 + 0.15 k at E <= 64, 8 above, d and c
+// not visible); b = 120 to 330 by the bins up to 128 experts, 720 and 1280 above (top-1: 120 to 300); d = 700 to 5900 and c =
+// 3.5 to 26 by the bins.  Without this limit, one
 // segment took, per call: E = 256, top-2, 374006 tokens 374 us with 256 workgroups against 40 with 8; E = 160, top-6, 200000
 // tokens 234 against 40 with 16; E = 64, top-8, 2 layers x 500000 tokens 112 against 55 with 128.
-int coact_num_workgroups(int64_t total, double segments, int32_t n_experts, int32_t top_k) {
+int coact_num_workgroups(int64_t total, double longest, double ends, int32_t n_experts, int32_t top_k) {
   static_assert(TACG_MAX_EXPERTS <= 256, "four classes of expert count");
-  constexpr double kSlot[4] = {150.0, 320.0, 720.0, 1280.0}, kEnd[4] = {1000.0, 2500.0, 4000.0, 6000.0}, kChip[4] = {8, 15, 20, 26};
+  constexpr double kSlotTop1[4] = {120, 190, 250, 300};
   const int q = std::min((n_experts - 1) / 64, 3);  // the workspace is also asked for beyond the supported sizes
+  const double bins = static_cast<double>(coact_bins(n_experts, top_k));
   const bool mfma = coact_uses_mfma(n_experts, top_k);
-  const double a = mfma ? (q == 0 ? 3.5 : 8.0) : 0.3 + 0.03 * top_k * (top_k - 1);
-  const double d = mfma ? 0.0 : kEnd[q], c = mfma ? 0.0 : kChip[q];
-  const double best = segments > 0 ? std::sqrt((total * a + segments * d) / (kSlot[q] / segments + c)) : 1.0;
+  const double a = mfma ? (q == 0 ? 3.0 + 0.15 * top_k : 8.0) : 0.3 + 0.03 * top_k * (top_k - 1);
+  const double b = top_k == 1 ? kSlotTop1[q] : q < 2 ? 120.0 + 0.026 * bins : q == 2 ? 720.0 : 1280.0;
+  const double d = mfma ? 0.0 : 700.0 + 0.16 * bins, c = mfma ? 0.0 : std::min(3.5 + bins / 700.0, 26.0);
+  const double best = longest > 0 ? std::sqrt((total * a + ends * d) / (b / longest + c)) : 1.0;
   if (coact_uses_mfma(n_experts, top_k)) return coact_mfma_workgroups(total, best, n_experts);
   // E > 128: the triangle needs more than half of the 160 KB LDS, so one 1024-thread workgroup per
   // CU; otherwise four 512-thread workgroups per CU (the same 32 waves, with four private triangles)
@@ -451,9 +454,13 @@ int launch_coact(const int16_t* trace, int64_t n_tokens, int32_t n_layers, int32
   a.E = n_experts;
   a.F = n_fam;
   // the longest segment's slots are the reduction's chain: as many segments of that length as the trace holds
-  int64_t longest = 1;
-  for (int f = 0; f < n_fam; ++f) longest = std::max(longest, fam_off_host[f + 1] - fam_off_host[f]);
-  a.W = coact_num_workgroups(a.total, static_cast<double>(a.total) / longest, n_experts, top_k);
+  int64_t longest = 1, families = 0;
+  for (int f = 0; f < n_fam; ++f) {
+    longest = std::max(longest, fam_off_host[f + 1] - fam_off_host[f]);
+    families += fam_off_host[f + 1] > fam_off_host[f];
+  }
+  a.W = coact_num_workgroups(a.total, static_cast<double>(a.total) / longest, static_cast<double>(families) * n_layers, n_experts,
+                             top_k);
   a.nbins = static_cast<int32_t>(coact_bins(n_experts, top_k));
   a.partial = static_cast<uint32_t*>(workspace);
   a.d_err = d_err;

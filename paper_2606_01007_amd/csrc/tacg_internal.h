@@ -43,8 +43,9 @@ struct Carver {
 };
 
 // ---- co-activation build -------------------------------------------------------------------
-// segments: (layer, family) segments with tokens, or fewer (see the definition); more of them never make fewer workgroups
-int coact_num_workgroups(int64_t total_token_layers, double segments, int32_t n_experts, int32_t top_k);
+// longest: the trace in lengths of its longest (layer, family) segment; ends: segments with tokens.  Neither is above
+// n_layers x n_fam, and more of them never make fewer workgroups
+int coact_num_workgroups(int64_t total_token_layers, double longest, double ends, int32_t n_experts, int32_t top_k);
 size_t coact_bins(int32_t n_experts, int32_t top_k);
 // small expert counts: the counts come from int8 matrix products (coact_mfma.hip)
 bool coact_uses_mfma(int32_t n_experts, int32_t top_k);

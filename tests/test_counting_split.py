@@ -17,7 +17,7 @@ def _workgroups(E, k, L, F, N):
 
 # the reduction of a segment reads the slots of its workgroups one after the other: few segments, few workgroups
 @pytest.mark.parametrize("E,k,L,F,N,lo,hi", [
-    (256, 2, 1, 1, 374006, 8, 16), (160, 6, 1, 1, 200000, 7, 32), (128, 2, 4, 4, 306464, 38, 256), (100, 2, 24, 16, 437668, 321, 800), (128, 8, 1, 1, 200000, 25, 128),
+    (256, 2, 1, 1, 374006, 8, 16), (160, 6, 1, 1, 200000, 7, 32), (128, 2, 4, 4, 306464, 38, 256), (100, 2, 24, 16, 437668, 321, 800), (128, 8, 1, 1, 200000, 25, 128), (60, 1, 12, 64, 124060, 400, 750),
     (64, 8, 2, 1, 500000, 64, 256), (256, 8, 58, 16, 4096, 230, 240), (128, 8, 48, 16, 16384, 700, 800), (256, 8, 58, 16, 1 << 21, 256, 256),
     (8, 2, 1, 1, 0, 1, 1),
 ])
@@ -29,7 +29,7 @@ def test_workgroups(E, k, L, F, N, lo, hi):
 def test_workgroups_grow_with_the_size(E, k):
     """A workspace for longer traces, more layers or more families also holds a smaller call."""
     for L, F in ((1, 1), (3, 2), (12, 8), (48, 64)):
-        w = [_workgroups(E, k, L, F, n) for n in (0, 1, 1000, 5000, 40000, 300000, 1 << 21, 1 << 24)]
+        w = [_workgroups(E, k, L, F, n) for n in (*range(0, 60000, 97), 300000, 1 << 21, 1 << 24)]
         assert w == sorted(w)
         assert _workgroups(E, k, L, F, 40000) <= _workgroups(E, k, L, F + 1, 40000)
 
